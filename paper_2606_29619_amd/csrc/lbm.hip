@@ -469,9 +469,9 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->analytic = p->grad_eps != nullptr;
     {
         // the fused correction-collision kernel: D3Q27, any storage, no solids, wet nodes,
-        // Picard iterations or analytic derivatives, whole tiles; AUTO takes
-        // it where the chunks are at least 16 planes long (shorter ones correct and stage too
-        // many end planes again)
+        // Picard iterations or analytic derivatives, whole tiles; AUTO takes it where 256
+        // workgroups leave each at least 16 planes (shorter chunks correct and stage too many
+        // end planes again)
         const bool half = p->storage == LBM_F16_SHIFTED || p->storage == LBM_BF16_SHIFTED;
         const int tx = p->storage == LBM_F64 ? lbm::ZCfg<double>::kX
                        : half               ? lbm::ZCfg<float, _Float16>::kX
@@ -484,7 +484,8 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
                           p->scheme == LBM_SCHEME_TWO_PASS && p->nx % tx == 0 && p->ny % ty == 0;
         if (able) h->ztiles = make_ztiling(p->nx, p->ny, p->nz, tx, ty);
         h->fused_vc = able && (p->passes == LBM_PASSES_FUSED ||
-                               (p->passes == LBM_PASSES_AUTO && h->ztiles.zc >= 16));
+                               (p->passes == LBM_PASSES_AUTO && p->nz >= 16 &&
+                                (int64_t)h->ztiles.ntx * h->ztiles.nty * p->nz >= 16 * 256));
     }
     if (hipGetDevice(&h->device) != hipSuccess) {
         delete h;

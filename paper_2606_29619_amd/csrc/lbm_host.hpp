@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -174,17 +175,29 @@ inline dim3 flat_grid(int64_t total) { return dim3((unsigned)((total + 255) / 25
 // marched through chunks of zc z-planes, the eight XCDs taking contiguous ranges of the
 // x-fastest, then y, then chunk order (neighbouring tiles in y share their ring rows in the
 // XCD's L2).  One workgroup fills a CU (LDS rings of 143 KB in FP32, 114 KB for the 16-bit
-// forms, 146 KB in FP64), so the chunks are as long as 256 workgroups allow, between 8 and 128
-// planes: long chunks correct and stage fewer end planes (256^3 box, FP32, an earlier version
-// of the kernel: chunks of 32, 64 and 128 planes 0.924, 0.936 and 0.906 ms).
+// forms, 146 KB in FP64), so the launch runs in rounds of 256 workgroups, 32 on each XCD, and
+// takes rounds x (zc + 3) plane times: a chunk corrects and stages about three planes' worth
+// before its first collision.  The chunk length with the smallest product is taken (the longest
+// of equals, at most 128 planes).  As long as 256 workgroups allow, which it was before, leaves
+// the second round nearly empty on many grids: 192^3 FP64 has 144 columns, 2 x 108 planes in
+// 288 workgroups took 1.32 ms, 7 x 28 planes in 1008 take 0.82 ms; 256^3 keeps its two chunks of
+// 128 planes.
 inline lbm::ZTiling make_ztiling(int nx, int ny, int nz, int tx, int ty) {
     lbm::ZTiling z{};
     z.ntx = nx / tx;
     z.nty = ny / ty;
     const int64_t cols = (int64_t)z.ntx * z.nty;
-    z.zc = (int)std::min<int64_t>(nz, std::max<int64_t>(8, std::min<int64_t>(128, cols * nz / 256)));
-    z.nch = (nz + z.zc - 1) / z.zc;
-    z.per = (uint32_t)((cols * z.nch + 7) / 8);
+    int64_t best = INT64_MAX;
+    for (int zc = std::min(nz, 128); zc >= std::min(nz, 4); --zc) {
+        const int nch = (nz + zc - 1) / zc;
+        const int64_t per = (cols * nch + 7) / 8;
+        const int64_t cost = (per + 31) / 32 * (zc + 3);
+        if (cost >= best) continue;
+        best = cost;
+        z.zc = zc;
+        z.nch = nch;
+        z.per = (uint32_t)per;
+    }
     return z;
 }
 

@@ -675,3 +675,20 @@ def test_fused_and_separate_passes_are_bitwise_equal(storage):
     assert torch.equal(a.populations(torch.float64), b.populations(torch.float64))
     for x, y in zip(a.moments(torch.float64), b.moments(torch.float64)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("storage,shape", [("f64", (37, 8, 64)), ("f32", (29, 8, 128)),
+                                           ("f16", (66, 16, 64)), ("f64", (130, 128, 192)),
+                                           ("bf16", (9, 256, 192))])
+def test_fused_chunk_lengths(storage, shape):
+    """z-chunks of the fused kernel chosen by the number of rounds: one-plane last chunks, more
+    than one round of workgroups and partial rounds; identical to the separate passes."""
+    w = workloads.random_porosity_3d(shape=shape, seed=31, ell=4.0)
+    st = {"f64": capi.LBM_F64, "f32": capi.LBM_F32, "f16": capi.LBM_F16_SHIFTED,
+          "bf16": capi.LBM_BF16_SHIFTED}[storage]
+    kw = dict(storage=st, shift=capi.LBM_SHIFT_POROUS)
+    a = capi.Solver.from_workload(w, passes=capi.LBM_PASSES_FUSED, **kw)
+    b = capi.Solver.from_workload(w, passes=capi.LBM_PASSES_SEPARATE, **kw)
+    ta, tb = a.step_timed(3), b.step_timed(3)
+    assert ta[1] == 0.0 and tb[1] > 0.0, (ta, tb)
+    assert torch.equal(a.populations(torch.float64), b.populations(torch.float64))
