@@ -230,7 +230,9 @@ typedef struct lbm_params {
      * where the run allows it: D3Q27, no solid cells, no wet-node boundaries, no Picard
      * iterations, no analytic porosity derivatives, nx a multiple of 64 and ny of 8 (4 for FP64
      * storage); LBM_PASSES_AUTO does so where, in addition, the grid is
-     * large enough for z-chunks of at least 16 planes (about 2^21 cells); every other run, and
+     * large enough for z-chunks of at least 16 planes (about 2^21 cells).  D2Q9 runs without
+     * wet-node boundaries, Picard iterations or analytic derivatives take the whole step in one
+     * launch under both, from one population buffer into a second.  Every other run, and
      * LBM_PASSES_SEPARATE, uses the separate correction pass.  All give bitwise the same
      * results. */
     int passes;
@@ -253,9 +255,11 @@ typedef struct lbm_stats {
 typedef struct lbm_solver lbm_solver;
 
 /*
- * Bytes of device workspace lbm_create needs for these parameters (pure host computation, no
- * device work).  Only lattice, storage, scheme, shift, nx, ny, nz, whether mask is non-NULL and
- * the number of boundary nodes in bc_type are read.
+ * Bytes of device workspace lbm_create uses for these parameters (pure host computation, no
+ * device work).  Only lattice, storage, scheme, shift, nx, ny, nz, passes, whether mask is non-NULL
+ * and the number of boundary nodes in bc_type are read.  D2Q9 two-pass runs that step in one launch
+ * (see lbm_params.passes) count a second population buffer here; lbm_create also takes a workspace
+ * without it (the footprint under LBM_PASSES_SEPARATE) and then steps in separate passes.
  * Errors: LBM_ERR_INVALID_ARG for NULL pointers or bad lattice, storage or dimensions.
  */
 LBM_API int lbm_footprint(const lbm_params *p, size_t *workspace_bytes);
@@ -288,9 +292,9 @@ LBM_API int lbm_step(lbm_solver *h, int64_t n);
  * As lbm_step, and also measures each kernel class with HIP events on the handle's stream;
  * synchronises.  kernel_ms[0..2] receive the summed durations (ms) of the moment, velocity
  * correction and collide-stream kernels over the n steps (lagged steps count their single
- * kernel under collide-stream; a two-pass step whose correction runs inside the collision pass,
- * see lbm_params.passes, reports 0 for the correction and the fused kernel under
- * collide-stream).
+ * kernel under collide-stream, as do D2Q9 steps of one launch; a two-pass step whose correction
+ * runs inside the collision pass, see lbm_params.passes, reports 0 for the correction and the
+ * fused kernel under collide-stream).
  */
 LBM_API int lbm_step_timed(lbm_solver *h, int64_t n, double kernel_ms[3]);
 

@@ -1,6 +1,6 @@
 """Build step of the HIP library: hipcc for gfx950 over the solver (differenced and analytic
-porosity-derivative halves) and the request-server sources, compiled in parallel and then
-linked; in-tree output."""
+porosity-derivative halves, one-launch D2Q9 step) and the request-server sources, compiled in
+parallel and then linked; in-tree output."""
 import os
 import shutil
 import subprocess
@@ -9,7 +9,8 @@ import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SRCS = [os.path.join(PKG, "csrc", f) for f in ("lbm.hip", "lbm_analytic.hip", "lbm_server.hip")]
+SRCS = [os.path.join(PKG, "csrc", f) for f in ("lbm.hip", "lbm_analytic.hip", "lbm_plane.hip",
+                                                "lbm_server.hip")]
 LIB = os.path.join(PKG, "liblbm.so")
 
 HIPCC_FLAGS = [
@@ -26,7 +27,7 @@ def build(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link liblbm.so.  hipcc compiles the device code of
     a source first and its host code afterwards, reading the headers a second time; the
     sources are therefore copied to a private directory first, so that both halves (and all
-    three sources) see the same text even if the tree changes while the build runs."""
+    four sources) see the same text even if the tree changes while the build runs."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory(prefix="lbm_build_") as tmpdir:
         src_dir = os.path.join(tmpdir, "csrc")

@@ -96,6 +96,16 @@ hipError_t one_step(lbm_solver *h, hipEvent_t *ev) {
         h->cur = nx;
     } else {
         const int c = h->cur;
+        if (h->plane_step) {
+            if (ev) e = hipEventRecord(ev[0], h->stream);
+            if (ev && e == hipSuccess) e = hipEventRecord(ev[1], h->stream);
+            launch_plane_step(h);
+            if (ev && e == hipSuccess) e = hipEventRecord(ev[2], h->stream);
+            if (e == hipSuccess) e = hipGetLastError();
+            h->phase ^= 1;
+            h->step += 1;
+            return e;
+        }
         if (h->fused_vc) {
             // velocity correction inside the collision pass (timed with it)
             dispatch(h, MomentsPass{h, h->L.m1[c]});
@@ -148,6 +158,13 @@ bool packed_rows_ok(const lbm_params *p) {
     const int tx = rect_tile_x(p->nx);
     const int padded = (p->nx + tx - 1) / tx * tx;
     return p->lattice == LBM_D3Q27 && 10 * (padded - p->nx) >= 3 * padded;
+}
+
+// Whole step in one launch (k_plane_step), from one population buffer into another: every
+// two-pass D2Q9 run without wet nodes, Picard iterations or analytic derivatives.
+bool plane_step_ok(const lbm_params *p, uint32_t nb) {
+    return p->lattice == LBM_D2Q9 && p->scheme == LBM_SCHEME_TWO_PASS && nb == 0 &&
+           p->picard_iters == 0 && !p->grad_eps && p->passes != LBM_PASSES_SEPARATE;
 }
 
 int validate_shape(const lbm_params *p, int *D, int *Q, size_t *sp, size_t *s, int64_t *N) {
@@ -325,6 +342,23 @@ int scratch_of_device(int dev, double **out) {
     return LBM_OK;
 }
 
+int run_layout(const lbm_params *p, Layout *L) {
+    int D, Q;
+    size_t sp, s;
+    int64_t N;
+    int rc = validate_shape(p, &D, &Q, &sp, &s, &N);
+    if (rc) return rc;
+    uint32_t nb = 0;
+    bool bo, bv, bvisc;
+    rc = boundary_nodes(p, D, N, &nb, &bo, &bv, &bvisc);
+    if (rc) return rc;
+    const lbm::Tiling tl = make_tiling(p->nx, p->ny, p->nz, packed_rows_ok(p));
+    *L = make_layout(Q, D, (size_t)N, sp, s, p->mask != nullptr, p->scheme == LBM_SCHEME_LAGGED,
+                     8 * (size_t)tl.per, nb, p->picard_iters > 0, p->grad_eps != nullptr,
+                     plane_step_ok(p, nb));
+    return LBM_OK;
+}
+
 }  // namespace lbmh
 
 using namespace lbmh;
@@ -353,20 +387,11 @@ LBM_API int lbm_lattice_info(int lattice, int *c_out, int *opp_out) {
 }
 
 LBM_API int lbm_footprint(const lbm_params *p, size_t *workspace_bytes) {
-    int D, Q;
-    size_t sp, s;
-    int64_t N;
     if (!workspace_bytes) return fail(LBM_ERR_INVALID_ARG, "workspace_bytes is NULL");
-    int rc = validate_shape(p, &D, &Q, &sp, &s, &N);
+    Layout L;
+    const int rc = run_layout(p, &L);
     if (rc) return rc;
-    uint32_t nb = 0;
-    bool bo, bv, bvisc;
-    rc = boundary_nodes(p, D, N, &nb, &bo, &bv, &bvisc);
-    if (rc) return rc;
-    const lbm::Tiling tl = make_tiling(p->nx, p->ny, p->nz, packed_rows_ok(p));
-    *workspace_bytes = make_layout(Q, D, (size_t)N, sp, s, p->mask != nullptr,
-                                   p->scheme == LBM_SCHEME_LAGGED, 8 * (size_t)tl.per, nb,
-                                   p->picard_iters > 0, p->grad_eps != nullptr).total;
+    *workspace_bytes = L.total;
     return LBM_OK;
 }
 
@@ -425,13 +450,14 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     const lbm::Tiling tiles = make_tiling(p->nx, p->ny, p->nz, packed_rows_ok(p));
     const Layout L = make_layout(Q, D, (size_t)N, sp, s, solids, p->scheme == LBM_SCHEME_LAGGED,
                                  8 * (size_t)tiles.per, nb, p->picard_iters > 0,
-                                 p->grad_eps != nullptr);
+                                 p->grad_eps != nullptr, plane_step_ok(p, nb));
     if (!dev_workspace) return fail(LBM_ERR_INVALID_ARG, "dev_workspace is NULL");
     if (reinterpret_cast<uintptr_t>(dev_workspace) % 256)
         return fail(LBM_ERR_WORKSPACE, "dev_workspace must be 256-byte aligned");
-    if (workspace_bytes < L.total)
+    // a workspace without room for the second population buffer steps in separate passes
+    if (workspace_bytes < L.base)
         return fail(LBM_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu bytes needed",
-                    workspace_bytes, L.total);
+                    workspace_bytes, L.base);
 
     lbm_solver *h = new (std::nothrow) lbm_solver();
     if (!h) return fail(LBM_ERR_INVALID_ARG, "out of host memory");
@@ -467,6 +493,7 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->picard_iters = p->picard_iters;
     h->picard_omega = p->picard_omega;
     h->analytic = p->grad_eps != nullptr;
+    h->plane_step = plane_step_ok(p, nb) && workspace_bytes >= L.total;
     {
         // the fused correction-collision kernel: D3Q27, any storage, no solids, wet nodes,
         // Picard iterations or analytic derivatives, whole tiles; AUTO takes it where 256
@@ -668,9 +695,11 @@ LBM_API int lbm_step_timed(lbm_solver *h, int64_t n, double kernel_ms[3]) {
         for (int64_t k = 0; k < m; ++k)
             for (int j = 0; j < 3; ++j) {
                 // a two-pass step with the correction inside the collision pass has no
-                // correction kernel: its share is 0 and the collision's interval spans both
-                if (h->fused_vc && h->scheme == LBM_SCHEME_TWO_PASS && j == 1) continue;
-                const int j0 = h->fused_vc && h->scheme == LBM_SCHEME_TWO_PASS && j == 2 ? 1 : j;
+                // correction kernel, one in a single launch only the collision's: the shares of
+                // the others are 0 and the collision's interval spans them
+                const int first = h->plane_step ? 0 : (h->fused_vc ? 1 : 2);
+                if (j >= first && j < 2) continue;
+                const int j0 = j == 2 ? first : j;
                 float ms = 0.f;
                 (void)hipEventElapsedTime(&ms, ev[3 * k + j0], ev[3 * k + j + 1]);
                 acc[j] += ms;

@@ -321,8 +321,8 @@ __device__ __forceinline__ void node_accel(const P4<T> *__restrict__ m2,
     Rec<T> rec[3][2];
     bool fl[3][2];
     load_stencil<D, T, SOLIDS>(nbr, ev, mask, g, nb, rec, fl);
-    accel_of<D, T, SOLIDS>(nbr, eps, muD, muF, mask, g, ph, nb, own, rec, fl, cs.ge, cs.H, cs.vs,
-                           acc);
+    const FarGlobal<D, T> far{nbr, eps, mask, &g, &nb};
+    accel_of<D, T, SOLIDS>(far, muD, muF, ph, nb, own, rec, fl, cs.ge, cs.H, cs.vs, acc);
 }
 
 // Rebuild of all post-advection populations of velocity and pressure nodes, lambda = dt = 1,

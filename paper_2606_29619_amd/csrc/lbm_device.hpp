@@ -650,15 +650,34 @@ __device__ __forceinline__ void load_stencil(const P4<T> *__restrict__ mom, cons
     }
 }
 
+// Fluid flag and record of the cell's second neighbour along axis a (k = -2 or 2), which only the
+// one-sided derivatives next to solids read: from the record and porosity arrays in memory.
+template <int D, typename T>
+struct FarGlobal {
+    const P4<T> *mom;
+    const T *eps;
+    const uint8_t *mask;
+    const Grid *g;
+    const Nbr<D> *nb;
+    __device__ __forceinline__ bool get(int a, int k, Rec<T> &q) const {
+        const uint32_t c = nb->axis(*g, a, k);
+        if (mask[c]) return false;
+        q = load_rec<D>(mom, c, ld(eps, c));
+        return true;
+    }
+};
+// Kernels without solids take no one-sided derivative.
+struct FarNone {
+    template <typename T>
+    __device__ __forceinline__ bool get(int, int, Rec<T> &) const { return false; }
+};
+
 // Variable-porosity viscous correction Delta_nu(m) at the cell, m = rho w / eps built from the
 // records, eq. (porosity_correction_expanded):
 //   nu {[H + tr(H) I] m + (div m) grad eps + (grad m) grad eps}
 //     + nu' [|grad eps|^2 m + (m . grad eps) grad eps],   [(grad m) grad eps]_a = sum_b d_b m_a d_b eps.
-template <int D, typename T, bool SOLIDS>
-__device__ __forceinline__ void delta_nu(const P4<T> *__restrict__ mom,
-                                         const T *__restrict__ eps,
-                                         const uint8_t *__restrict__ mask, const Grid &g,
-                                         const Nbr<D> &nb, const Rec<T> &own,
+template <int D, typename T, bool SOLIDS, typename FAR>
+__device__ __forceinline__ void delta_nu(const FAR &far, const Rec<T> &own,
                                          const Rec<T> rec[3][2], const bool fl[3][2],
                                          const T ge[3], const T H[3][3], const Visc<T> &vs,
                                          T out[3]) {
@@ -676,15 +695,14 @@ __device__ __forceinline__ void delta_nu(const P4<T> *__restrict__ mom,
         } else {
             bool f5[5] = {false, fl[a][0], true, fl[a][1], false};
             T m2m[3] = {T(0), T(0), T(0)}, m2p[3] = {T(0), T(0), T(0)};
+            Rec<T> q2;
             if (fl[a][1] && !fl[a][0]) {
-                const uint32_t p2 = nb.axis(g, a, 2);
-                f5[4] = !mask[p2];
-                if (f5[4]) rec_m<D>(load_rec<D>(mom, p2, ld(eps, p2)), m2p);
+                f5[4] = far.get(a, 2, q2);
+                if (f5[4]) rec_m<D>(q2, m2p);
             }
             if (fl[a][0] && !fl[a][1]) {
-                const uint32_t m2 = nb.axis(g, a, -2);
-                f5[0] = !mask[m2];
-                if (f5[0]) rec_m<D>(load_rec<D>(mom, m2, ld(eps, m2)), m2m);
+                f5[0] = far.get(a, -2, q2);
+                if (f5[0]) rec_m<D>(q2, m2m);
             }
 #pragma unroll
             for (int b = 0; b < D; ++b) {
@@ -719,42 +737,36 @@ __device__ __forceinline__ void delta_nu(const P4<T> *__restrict__ mom,
 }
 
 // Derivative along axis a of a scalar built from a record (Phi^ext's flux, or v_a).
-template <int D, typename T, bool SOLIDS, typename F>
-__device__ __forceinline__ T record_deriv(const P4<T> *__restrict__ mom,
-                                          const T *__restrict__ eps,
-                                          const uint8_t *__restrict__ mask, const Grid &g,
-                                          const Nbr<D> &nb, int a, const Rec<T> &own,
+template <int D, typename T, bool SOLIDS, typename FAR, typename F>
+__device__ __forceinline__ T record_deriv(const FAR &far, int a, const Rec<T> &own,
                                           const Rec<T> rec[3][2], const bool fl[3][2], F fn) {
     const T vm = fn(rec[a][0]), vp = fn(rec[a][1]);
     if (!SOLIDS || (fl[a][0] && fl[a][1])) return (vp - vm) * T(0.5);
     bool f5[5] = {false, fl[a][0], true, fl[a][1], false};
     T v5[5] = {T(0), vm, fn(own), vp, T(0)};
+    Rec<T> q2;
     if (fl[a][1] && !fl[a][0]) {
-        const uint32_t p2 = nb.axis(g, a, 2);
-        f5[4] = !mask[p2];
-        if (f5[4]) v5[4] = fn(load_rec<D>(mom, p2, ld(eps, p2)));
+        f5[4] = far.get(a, 2, q2);
+        if (f5[4]) v5[4] = fn(q2);
     }
     if (fl[a][0] && !fl[a][1]) {
-        const uint32_t m2 = nb.axis(g, a, -2);
-        f5[0] = !mask[m2];
-        if (f5[0]) v5[0] = fn(load_rec<D>(mom, m2, ld(eps, m2)));
+        f5[0] = far.get(a, -2, q2);
+        if (f5[0]) v5[0] = fn(q2);
     }
     return deriv_rule(v5, f5);
 }
 
 // Acceleration (accel) with Delta_nu(rho v / eps) from the record stencil (porosity_correction).
-template <int D, typename T, bool SOLIDS>
-__device__ __forceinline__ void accel_of(const P4<T> *__restrict__ mom,
-                                         const T *__restrict__ eps, const T *__restrict__ muD,
-                                         const T *__restrict__ muF,
-                                         const uint8_t *__restrict__ mask, const Grid &g,
-                                         const Phys<T> &ph, const Nbr<D> &nb, const Rec<T> &own,
+template <int D, typename T, bool SOLIDS, typename FAR>
+__device__ __forceinline__ void accel_of(const FAR &far, const T *__restrict__ muD,
+                                         const T *__restrict__ muF, const Phys<T> &ph,
+                                         const Nbr<D> &nb, const Rec<T> &own,
                                          const Rec<T> rec[3][2], const bool fl[3][2],
                                          const T ge[3], const T H[3][3], const Visc<T> &vs,
                                          T acc[3]) {
     const uint32_t n = nb.self();
     T dm[3] = {T(0), T(0), T(0)};
-    delta_nu<D, T, SOLIDS>(mom, eps, mask, g, nb, own, rec, fl, ge, H, vs, dm);
+    delta_nu<D, T, SOLIDS>(far, own, rec, fl, ge, H, vs, dm);
     T s = T(0);
 #pragma unroll
     for (int a = 0; a < D; ++a) s = s + own.w[a] * own.w[a];
@@ -771,17 +783,16 @@ __device__ __forceinline__ void accel_of(const P4<T> *__restrict__ mom,
 // Equilibrium and shifted-equilibrium arguments of one cell from the moment fields (rho, v):
 // acceleration (accel), Phi^ext (ex_corr), Phi^eta (eta_corr), then xi, P (xi_alpha_eq,
 // P_alpha_alpha_eq) and xi*, P* (xi_alpha_*, P_aa_*) with lambda = 1.  `own` is the cell's
-// record and rec / fl its axis neighbours; `mom` (the same step's records, or the previous
+// record and rec / fl its axis neighbours; `far` (the same step's records, or the previous
 // step's in the lagged scheme) is read only for the one-sided stencils next to solids.
-template <int D, typename T, bool SOLIDS, typename E>
+template <int D, typename T, bool SOLIDS, typename FAR>
 __device__ __forceinline__ void forcing_args_stencil(
-    const P4<T> *__restrict__ mom, const E &ev, const T *__restrict__ eps,
-    const T *__restrict__ muD, const T *__restrict__ muF, const uint8_t *__restrict__ mask,
-    const Grid &g, const Phys<T> &ph, const Nbr<D> &nb, const Rec<T> &own,
+    const FAR &far, const T *__restrict__ muD, const T *__restrict__ muF, const Phys<T> &ph,
+    const Nbr<D> &nb, const Rec<T> &own,
     const Rec<T> rec[3][2], const bool fl[3][2], const T ge[3], const T H[3][3],
     const Visc<T> &vs, T xi[3], T P[3], T xs[3], T Ps[3]) {
     T acc[3];
-    accel_of<D, T, SOLIDS>(mom, eps, muD, muF, mask, g, ph, nb, own, rec, fl, ge, H, vs, acc);
+    accel_of<D, T, SOLIDS>(far, muD, muF, ph, nb, own, rec, fl, ge, H, vs, acc);
     T phx[3];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
@@ -790,7 +801,7 @@ __device__ __forceinline__ void forcing_args_stencil(
             const T va = q.w[a];
             return (q.r * va) * omr - dv(q.r * ((va * va) * va), q.e * q.e);
         };
-        phx[a] = record_deriv<D, T, SOLIDS>(mom, eps, mask, g, nb, a, own, rec, fl, gext);
+        phx[a] = record_deriv<D, T, SOLIDS>(far, a, own, rec, fl, gext);
     }
     T pheta = T(0);
     if (ph.eta_on) {
@@ -798,7 +809,7 @@ __device__ __forceinline__ void forcing_args_stencil(
 #pragma unroll
         for (int a = 0; a < D; ++a) {
             auto va = [a](const Rec<T> &q) { return q.w[a]; };
-            divv = divv + record_deriv<D, T, SOLIDS>(mom, eps, mask, g, nb, a, own, rec, fl, va);
+            divv = divv + record_deriv<D, T, SOLIDS>(far, a, own, rec, fl, va);
         }
         pheta = ((own.r * ph.RT) * (ph.two_over_D - dv(ph.eta, vs.nu))) * divv;
     }
@@ -826,8 +837,9 @@ __device__ __forceinline__ void forcing_args(const P4<T> *__restrict__ mom, cons
     Rec<T> rec[3][2];
     bool fl[3][2];
     load_stencil<D, T, SOLIDS>(mom, ev, mask, g, nb, rec, fl);
-    forcing_args_stencil<D, T, SOLIDS>(mom, ev, eps, muD, muF, mask, g, ph, nb, own, rec, fl, ge,
-                                       H, vs, xi, P, xs, Ps);
+    const FarGlobal<D, T> far{mom, eps, mask, &g, &nb};
+    forcing_args_stencil<D, T, SOLIDS>(far, muD, muF, ph, nb, own, rec, fl, ge, H, vs, xi, P, xs,
+                                       Ps);
 }
 
 // One-dimensional factors of eq. (1d_scaled_eq) for c = -1, 0, +1.
@@ -897,17 +909,14 @@ __device__ __forceinline__ bool porosity_flat(const CellStatic<D, T> &cs) {
 // Velocity correction (v_final) from the cell's record and its axis neighbours rec / fl:
 // v = v^(1) + Delta_nu(rho v^(1) / eps) / (2 rho); on flat porosity v = v^(1) + 0 (the value of
 // the full evaluation) and the stencil is not used.
-template <int D, typename T, bool SOLIDS>
-__device__ __forceinline__ void velocity_from_stencil(const P4<T> *__restrict__ m1,
-                                                      const T *__restrict__ eps,
-                                                      const uint8_t *__restrict__ mask,
-                                                      const Grid &g, const Nbr<D> &nb,
-                                                      const Rec<T> &own, const Rec<T> rec[3][2],
+template <int D, typename T, bool SOLIDS, typename FAR>
+__device__ __forceinline__ void velocity_from_stencil(const FAR &far, const Rec<T> &own,
+                                                      const Rec<T> rec[3][2],
                                                       const bool fl[3][2],
                                                       const CellStatic<D, T> &cs, bool flat,
                                                       T v[3]) {
     T dn[3] = {T(0), T(0), T(0)};
-    if (!flat) delta_nu<D, T, SOLIDS>(m1, eps, mask, g, nb, own, rec, fl, cs.ge, cs.H, cs.vs, dn);
+    if (!flat) delta_nu<D, T, SOLIDS>(far, own, rec, fl, cs.ge, cs.H, cs.vs, dn);
 #pragma unroll
     for (int a = 0; a < 3; ++a) v[a] = T(0);
 #pragma unroll
@@ -927,7 +936,8 @@ __device__ __forceinline__ void corrected_velocity(const P4<T> *__restrict__ m1,
     Rec<T> rec[3][2];
     bool fl[3][2];
     if (!flat) load_stencil<D, T, SOLIDS>(m1, ev, mask, g, nb, rec, fl);
-    velocity_from_stencil<D, T, SOLIDS>(m1, eps, mask, g, nb, own, rec, fl, cs, flat, v);
+    const FarGlobal<D, T> far{m1, eps, mask, &g, &nb};
+    velocity_from_stencil<D, T, SOLIDS>(far, own, rec, fl, cs, flat, v);
 }
 
 // Equilibria of the cell (prod_form) for the equilibrium and shifted-equilibrium arguments.
@@ -1388,7 +1398,8 @@ __device__ __forceinline__ void picard_body(const P4<T> *__restrict__ vin,
     bool fl[3][2];
     load_stencil<D, T, SOLIDS>(vin, ev, mask, g, nb, rec, fl);
     T dn[3];
-    delta_nu<D, T, SOLIDS>(vin, eps, mask, g, nb, own, rec, fl, cs.ge, cs.H, cs.vs, dn);
+    const FarGlobal<D, T> far{vin, eps, mask, &g, &nb};
+    delta_nu<D, T, SOLIDS>(far, own, rec, fl, cs.ge, cs.H, cs.vs, dn);
     const P4<T> q0 = ld(m0, n);
     const T v0[3] = {q0.y, q0.z, q0.w};
     T sv[3] = {T(0), T(0), T(0)};
@@ -1731,9 +1742,7 @@ __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__re
                 for (int a = 0; a < 3; ++a) fl[a][0] = fl[a][1] = true;
             }
             T v[3];
-            const Nbr<D> none{};
-            velocity_from_stencil<D, T, false>(nullptr, nullptr, nullptr, g, none, own, rec, fl,
-                                               cs, flat, v);
+            velocity_from_stencil<D, T, false>(FarNone{}, own, rec, fl, cs, flat, v);
             dst[j] = pack(own.r, v[0], v[1], v[2]);
         }
     };
@@ -1798,8 +1807,8 @@ __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__re
 #pragma unroll
             for (int a = 0; a < 3; ++a) fl[a][0] = fl[a][1] = true;
             T xi[3], P[3], xs[3], Ps[3];
-            forcing_args_stencil<D, T, false>(nullptr, ev, eps, muD, muF, nullptr, g, ph, nb, own,
-                                              rec, fl, cs.ge, cs.H, cs.vs, xi, P, xs, Ps);
+            forcing_args_stencil<D, T, false>(FarNone{}, muD, muF, ph, nb, own, rec, fl, cs.ge,
+                                              cs.H, cs.vs, xi, P, xs, Ps);
             ProductForm<D, T> peq, pst;
             const T er = own.e * own.r;
             peq.init(er, xi, P);

@@ -54,6 +54,8 @@ struct Layout {
     size_t deps;                // analytic porosity derivatives, D + D(D+1)/2 planes
     size_t tsolid;              // per-tile flag: a solid cell within one cell of the tile
     size_t tflat;               // per-tile flag: a porosity gradient somewhere in the tile
+    size_t f2;                  // second population buffer (runs stepped in one launch)
+    size_t base;                // bytes without f2: what a run needs at least
     size_t total;
 };
 
@@ -61,7 +63,7 @@ struct Layout {
 // ntiles: workgroups of the tiled passes (solid runs keep one flag byte per tile).
 inline Layout make_layout(int Q, int D, size_t N, size_t sp, size_t s, bool solids, bool lagged,
                           size_t ntiles, size_t nbnodes = 0, bool picard = false,
-                          bool analytic = false) {
+                          bool analytic = false, bool second = false) {
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -92,6 +94,8 @@ inline Layout make_layout(int Q, int D, size_t N, size_t sp, size_t s, bool soli
     L.deps = analytic ? take((size_t)(D + D * (D + 1) / 2) * N * s) : 0;
     L.tsolid = solids ? take(ntiles) : 0;
     L.tflat = analytic ? 0 : take(ntiles);
+    L.base = off;
+    L.f2 = second ? take((size_t)Q * N * sp) : 0;
     L.total = off;
     return L;
 }
@@ -125,6 +129,7 @@ struct lbm_solver {
     bool analytic;      // analytic porosity derivatives in L.deps
     lbm::Tiling tiles;  // 256-cell tiles, blocked, in XCD-contiguous ranges
     bool fused_vc;      // velocity correction inside the collision pass (k_collide_vc)
+    bool plane_step;    // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
     bool solid_occ;     // runs with solids: under a quarter of the tiles solid-aware
     lbm::ZTiling ztiles;
     int device;         // HIP device current at creation
@@ -243,6 +248,9 @@ T *ws_ptr(const lbm_solver *h, size_t off) {
     return reinterpret_cast<T *>(h->ws + off);
 }
 
+// Offset of the population buffer that holds the current state.
+inline size_t f_off(const lbm_solver *h) { return h->plane_step && h->phase ? h->L.f2 : h->L.f; }
+
 inline const uint8_t *mask_ptr(const lbm_solver *h) {
     return h->solids ? reinterpret_cast<const uint8_t *>(h->ws + h->L.mask) : nullptr;
 }
@@ -255,6 +263,12 @@ inline const uint8_t *tsolid_ptr(const lbm_solver *h) {
 inline const uint8_t *tflat_ptr(const lbm_solver *h) {
     return h->analytic ? nullptr : reinterpret_cast<const uint8_t *>(h->ws + h->L.tflat);
 }
+
+// Workspace layout of a run with the shape and options of p (validates them; host only).
+int run_layout(const lbm_params *p, Layout *L);
+
+// Enqueue one D2Q9 step of a run with plane_step (lbm_plane.hip).
+void launch_plane_step(const lbm_solver *h);
 
 // Enqueue the statistics of the current state into res (8 doubles, the lbm_stats slots) with the
 // per-block partial sums in part, without synchronising; defined with the solver kernels.

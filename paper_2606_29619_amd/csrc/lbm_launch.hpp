@@ -20,7 +20,7 @@ void launch_moments(const lbm_solver *h, size_t m1_out) {
     auto ph = phys_of<T>(h);
     lbm::P4<T> *m0 = h->picard_iters ? ws_ptr<lbm::P4<T>>(h, h->L.m0) : nullptr;
     hipLaunchKernelGGL((lbm::k_moments<D, T, P, S, PH, AD>), cell_tiles(h), dim3(256), 0, h->stream,
-                       ws_ptr<const P>(h, h->L.f), ws_ptr<const T>(h, h->L.eps),
+                       ws_ptr<const P>(h, f_off(h)), ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
                        tsolid_ptr(h), ws_ptr<lbm::P4<T>>(h, m1_out), m0, grid_of(h), h->tiles, ph);
 }
@@ -48,7 +48,7 @@ template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
 void launch_collide_occ(const lbm_solver *h, size_t m2, size_t nbr) {
     auto ph = phys_of<T>(h);
     hipLaunchKernelGGL((lbm::k_collide<D, T, P, S, PH, AD, OCC>), cell_tiles(h), dim3(256), 0,
-                       h->stream, ws_ptr<P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, m2),
+                       h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                        ws_ptr<const lbm::P4<T>>(h, nbr),
                        ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
@@ -72,7 +72,7 @@ template <int D, typename T, typename P, bool S, int PH>
 void launch_collide_vc(const lbm_solver *h, size_t m1) {
     if constexpr (D == 3 && !S)
         hipLaunchKernelGGL((lbm::k_collide_vc<T, P, PH>), dim3(8 * h->ztiles.per), dim3(lbm::ZCfg<T, P>::kThreads), 0,
-                           h->stream, ws_ptr<P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, m1),
+                           h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m1),
                            ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                            ws_ptr<const T>(h, h->L.muF), grid_of(h), h->ztiles, phys_of<T>(h));
 }
@@ -81,7 +81,7 @@ template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
 void launch_fused_occ(const lbm_solver *h, int prev, int next) {
     auto ph = phys_of<T>(h);
     hipLaunchKernelGGL((lbm::k_fused<D, T, P, S, PH, AD, OCC>), cell_tiles(h), dim3(256), 0, h->stream,
-                       ws_ptr<P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, h->L.m1[prev]),
+                       ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, h->L.m1[prev]),
                        ws_ptr<const lbm::P4<T>>(h, h->L.m2[prev]),
                        ws_ptr<lbm::P4<T>>(h, h->L.m1[next]), ws_ptr<lbm::P4<T>>(h, h->L.m2[next]),
                        ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
@@ -104,7 +104,7 @@ template <int D, typename T, typename P, bool S, bool AD>
 void launch_init(const lbm_solver *h) {
     auto ph = phys_of<T>(h);
     hipLaunchKernelGGL((lbm::k_init<D, T, P, S, AD>), cell_tiles(h), dim3(256), 0, h->stream,
-                       ws_ptr<P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, h->L.m2[0]),
+                       ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, h->L.m2[0]),
                        ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
                        grid_of(h), h->tiles, ph);
@@ -113,14 +113,14 @@ void launch_init(const lbm_solver *h) {
 template <int D, typename T, typename P, bool S, int PH, typename O>
 void launch_export(const lbm_solver *h, O *out) {
     hipLaunchKernelGGL((lbm::k_export<D, T, P, S, PH, O>), cell_tiles(h), dim3(256), 0,
-                       h->stream, ws_ptr<const P>(h, h->L.f), mask_ptr(h),
+                       h->stream, ws_ptr<const P>(h, f_off(h)), mask_ptr(h),
                        ws_ptr<const T>(h, h->L.eps), out, grid_of(h), h->tiles, phys_of<T>(h));
 }
 
 template <int D, typename T, typename P, bool S, typename I>
 void launch_import(const lbm_solver *h, const I *in) {
     hipLaunchKernelGGL((lbm::k_import<D, T, P, S, I>), cell_tiles(h), dim3(256), 0, h->stream,
-                       ws_ptr<P>(h, h->L.f), in, mask_ptr(h), ws_ptr<const T>(h, h->L.eps),
+                       ws_ptr<P>(h, f_off(h)), in, mask_ptr(h), ws_ptr<const T>(h, h->L.eps),
                        grid_of(h), h->tiles, phys_of<T>(h));
 }
 
@@ -132,7 +132,7 @@ inline int stats_blocks(const lbm_solver *h) {
 template <int D, typename T, typename P, bool S, int PH>
 void launch_stats(const lbm_solver *h, size_t m2, double *part) {
     hipLaunchKernelGGL((lbm::k_stats<D, T, P, S, PH>), dim3(stats_blocks(h)), dim3(256), 0,
-                       h->stream, ws_ptr<const P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, m2),
+                       h->stream, ws_ptr<const P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                        ws_ptr<T>(h, h->L.vsnap), mask_ptr(h), ws_ptr<const T>(h, h->L.eps),
                        part, grid_of(h), phys_of<T>(h));
 }
@@ -151,7 +151,7 @@ struct BcOutflowPass {
     void operator()() {
         if constexpr (S)
             hipLaunchKernelGGL((lbm::k_bc_outflow<D, T, P, S, PH>), flat_grid(h->nb), dim3(256), 0,
-                               h->stream, ws_ptr<P>(h, h->L.f), mask_ptr(h),
+                               h->stream, ws_ptr<P>(h, f_off(h)), mask_ptr(h),
                                ws_ptr<const T>(h, h->L.eps), bnodes_of<T>(h), grid_of(h),
                                phys_of<T>(h));
     }
@@ -165,7 +165,7 @@ struct BcRecordsPass {
     void operator()() {
         if constexpr (S)
             hipLaunchKernelGGL((lbm::k_bc_records<D, T, P, S, PH, AD>), flat_grid(h->nb), dim3(256), 0,
-                               h->stream, ws_ptr<const P>(h, h->L.f), mask_ptr(h),
+                               h->stream, ws_ptr<const P>(h, f_off(h)), mask_ptr(h),
                                ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                                ws_ptr<const T>(h, h->L.muF), ws_ptr<lbm::P4<T>>(h, m1),
                                bnodes_of<T>(h), grid_of(h), phys_of<T>(h),
@@ -192,7 +192,7 @@ struct BcRebuildPass {  // own records m2, stencil neighbours' nbr
     void operator()() {
         if constexpr (S)
             hipLaunchKernelGGL((lbm::k_bc_rebuild<D, T, P, S, PH, AD>), flat_grid(h->nb), dim3(256), 0,
-                               h->stream, ws_ptr<P>(h, h->L.f), ws_ptr<const lbm::P4<T>>(h, m2),
+                               h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                                ws_ptr<const lbm::P4<T>>(h, nbr),
                                ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                                ws_ptr<const T>(h, h->L.muF), mask_ptr(h), bnodes_of<T>(h),

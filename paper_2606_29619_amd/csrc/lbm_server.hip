@@ -409,9 +409,11 @@ LBM_API int lbm_server_submit(lbm_server *s, const lbm_params *p, double tol, in
     if (!(tol > 0) || max_steps < s->check_every)
         return fail(LBM_ERR_INVALID_ARG, "tol must be > 0 and max_steps >= check_every");
     if (floor_checks < 0) return fail(LBM_ERR_INVALID_ARG, "floor_checks must be >= 0");
-    size_t bytes = 0;
-    rc = lbm_footprint(p, &bytes);
+    // what the run needs at least: the batched launches step in place
+    Layout layout;
+    rc = run_layout(p, &layout);
     if (rc) return rc;
+    const size_t bytes = layout.base;
     if (align256(bytes) > s->pool_bytes - align256(kTableBytes))
         return fail(LBM_ERR_WORKSPACE, "a workspace of %zu bytes can never fit the pool", bytes);
     if (!p->eps || !p->kappa || !p->forch) return fail(LBM_ERR_INVALID_ARG, "eps, kappa and forch are required");
