@@ -161,9 +161,12 @@ bool packed_rows_ok(const lbm_params *p) {
 }
 
 // Whole step in one launch (k_plane_step), from one population buffer into another: every
-// two-pass D2Q9 run without wet nodes, Picard iterations or analytic derivatives.
+// two-pass D2Q9 run of 256 cells and more without wet nodes, Picard iterations or analytic
+// derivatives.  A smaller grid has fewer cells than one workgroup has threads, its tile's rings wrap
+// onto the tile several times over, and it keeps the separate passes and their workspace size.
 bool plane_step_ok(const lbm_params *p, uint32_t nb) {
     return p->lattice == LBM_D2Q9 && p->scheme == LBM_SCHEME_TWO_PASS && nb == 0 &&
+           (int64_t)p->nx * p->ny >= 256 &&
            p->picard_iters == 0 && !p->grad_eps && p->passes != LBM_PASSES_SEPARATE;
 }
 

@@ -32,14 +32,14 @@ def _equal(a, b):
         assert torch.equal(x, y)
 
 
-# (ny, nx): narrower than a tile and its rings, one tile exactly, ragged tiles, the last size of
-# the small tile and the first of the large one, a large ragged plane
-@pytest.mark.parametrize("shape", [(1, 2), (2, 3), (8, 8), (9, 31), (61, 67), (255, 257),
-                                   (256, 256), (131, 1019)])
+# (ny, nx): narrower than a tile and its rings along either axis (rings wrap several times), whole
+# tiles, ragged tiles, the last size of the small tile and the first of the large one, a large plane
+@pytest.mark.parametrize("shape", [(1, 256), (260, 1), (3, 90), (130, 2), (16, 16), (9, 31),
+                                   (61, 67), (255, 257), (256, 256), (131, 1019)])
 @pytest.mark.parametrize("storage,shift", [("f64", 0), ("f32", 0), ("f16", 1), ("bf16", 0)])
 @pytest.mark.parametrize("solids", [False, True])
 def test_one_launch_step_equals_separate_passes(shape, storage, shift, solids):
-    if solids and shape[0] < 8:
+    if solids and min(shape) < 8:
         pytest.skip("no room for solid cells")
     w = _workload(shape, solids)
     kw = dict(storage=STORAGE[storage], shift=shift)
