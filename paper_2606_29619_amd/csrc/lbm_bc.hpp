@@ -109,13 +109,19 @@ __device__ __forceinline__ void write_read_slot(P *__restrict__ f,
         encode<D, I, P>(v, load_sigma<D, SOLIDS, I, P>(mask, ev, ph, nb));
 }
 
+// One thread per node, one wave per workgroup: a duct's faces hold some 10^5 nodes, which fill the
+// chip's 256 CUs evenly only in small workgroups (384 x 192 x 192 duct, 72,200 nodes, workgroups of
+// 256 and of 64 threads: FP32 rebuild 173 and 138 us, records 75 and 56 us; both reach a cache line
+// of every population plane per node of an x face).
+constexpr unsigned kBcThreads = 64;
+
 // Zero-gradient outflow: f_I(x_b) = f_I(x_f) for I in P-.
 template <int D, typename T, typename P, bool SOLIDS, int PH>
-__global__ __launch_bounds__(256) void k_bc_outflow(P *__restrict__ f,
+__global__ __launch_bounds__(kBcThreads) void k_bc_outflow(P *__restrict__ f,
                                                     const uint8_t *__restrict__ mask,
                                                     const T *__restrict__ eps, BNodes<T> bn,
                                                     Grid g, Phys<T> ph) {
-    const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t k = blockIdx.x * kBcThreads + threadIdx.x;
     if (k >= bn.count) return;
     const uint32_t code = bn.code[k];
     if ((code & 0xffu) != kNodeOutflow) return;
@@ -206,7 +212,7 @@ __device__ __forceinline__ T bc_viscous_term(const P4<T> *__restrict__ m1,
 //   a_perp, from the velocities stage 0 left in the records.  Other threads read only the
 //   velocity of a node's record, which this stage rewrites with the same value.
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
-__global__ __launch_bounds__(256) void k_bc_records(const P *__restrict__ f,
+__global__ __launch_bounds__(kBcThreads) void k_bc_records(const P *__restrict__ f,
                                                     const uint8_t *__restrict__ mask,
                                                     const T *__restrict__ eps,
                                                     const T *__restrict__ muD,
@@ -214,7 +220,7 @@ __global__ __launch_bounds__(256) void k_bc_records(const P *__restrict__ f,
                                                     P4<T> *__restrict__ m1, BNodes<T> bn, Grid g,
                                                     Phys<T> ph, int bounce_back_density,
                                                     int stage) {
-    const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t k = blockIdx.x * kBcThreads + threadIdx.x;
     if (k >= bn.count) return;
     const uint32_t code = bn.code[k];
     const uint32_t type = code & 0xffu;
@@ -282,9 +288,9 @@ __global__ __launch_bounds__(256) void k_bc_records(const P *__restrict__ f,
 
 // After the velocity correction: the corrected velocity of velocity and pressure nodes is v_b.
 template <typename T>
-__global__ __launch_bounds__(256) void k_bc_fix(const P4<T> *__restrict__ m1,
+__global__ __launch_bounds__(kBcThreads) void k_bc_fix(const P4<T> *__restrict__ m1,
                                                 P4<T> *__restrict__ m2, BNodes<T> bn) {
-    const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t k = blockIdx.x * kBcThreads + threadIdx.x;
     if (k >= bn.count) return;
     const uint32_t type = bn.code[k] & 0xffu;
     if (type != kNodeVelocity && type != kNodePressure) return;
@@ -332,7 +338,7 @@ __device__ __forceinline__ void node_accel(const P4<T> *__restrict__ m2,
 //     f_i = zeta f_i(x_f) + (3/2)[f^tgt_i - zeta f^eq_i(x_f)] + (1/2)[zeta f^*_i(x_f) - f^*_i];
 //   scheme 2, TMS (Sec. 3.4.4, steps 1-3).
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
-__global__ __launch_bounds__(256) void k_bc_rebuild(P *__restrict__ f,
+__global__ __launch_bounds__(kBcThreads) void k_bc_rebuild(P *__restrict__ f,
                                                     const P4<T> *__restrict__ m2,
                                                     const P4<T> *__restrict__ nbr,
                                                     const T *__restrict__ eps,
@@ -342,7 +348,7 @@ __global__ __launch_bounds__(256) void k_bc_rebuild(P *__restrict__ f,
                                                     BNodes<T> bn, Grid g, Phys<T> ph,
                                                     int scheme) {
     using L = Lat<D>;
-    const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t k = blockIdx.x * kBcThreads + threadIdx.x;
     if (k >= bn.count) return;
     const uint32_t code = bn.code[k];
     const uint32_t type = code & 0xffu;

@@ -405,9 +405,7 @@ __device__ __forceinline__ uint32_t source_cell(const uint8_t *__restrict__ mask
         return nb.self();
     } else {
         const uint32_t s = nb.at(-cx, -cy, -cz);
-        if constexpr (SOLIDS) {
-            if (mask[s]) return nb.self();
-        }
+        if constexpr (SOLIDS) return mask[s] ? nb.self() : s;
         return s;
     }
 }
@@ -424,8 +422,9 @@ __device__ __forceinline__ P load_raw(const P *__restrict__ f, const uint8_t *__
         return ld_pop<NT>(plane(f, I, g.N), n);
     } else {
         const uint32_t s = nb.at(-cx, -cy, -cz);
-        if constexpr (SOLIDS) {
-            if (mask[s]) return ld_pop<NT>(plane(f, I, g.N), n);
+        if constexpr (SOLIDS) {  // an address select: a branch would wait for each flag in turn
+            const bool back = mask[s] != 0;
+            return ld_pop<NT>(plane(f, back ? I : L::opp[I], g.N), back ? n : s);
         }
         return ld_pop<NT>(plane(f, L::opp[I], g.N), s);
     }
@@ -442,9 +441,12 @@ __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, co
         using L = Lat<D>;
         constexpr int cx = L::c[I][0], cy = L::c[I][1], cz = L::c[I][2];
         if (!ph.shift_porous) return shift_sigma<D, I, P>(T(1), ph);
-        const bool own = (cx == 0 && cy == 0 && cz == 0) ||
-                         (SOLIDS && source_cell<D, SOLIDS, I>(mask, nb) == nb.self());
-        return shift_sigma<D, I, P>(own ? ev.at(0, 0, 0) : ev.at(-cx, -cy, -cz), ph);
+        T e = ev.at(-cx, -cy, -cz);
+        if constexpr (SOLIDS && (cx != 0 || cy != 0 || cz != 0)) {
+            const T e0 = ev.at(0, 0, 0);
+            if (source_cell<D, SOLIDS, I>(mask, nb) == nb.self()) e = e0;
+        }
+        return shift_sigma<D, I, P>(e, ph);
     }
 }
 
@@ -471,12 +473,11 @@ __device__ __forceinline__ void store_pop(P *__restrict__ f, const uint8_t *__re
     } else {
         const uint32_t d = nb.at(cx, cy, cz);
         if constexpr (SOLIDS) {
-            if (mask[d]) {
-                st_pop<NT>(plane(f, L::opp[I], g.N), n, raw);
-                return;
-            }
+            const bool back = mask[d] != 0;
+            st_pop<NT>(plane(f, back ? L::opp[I] : I, g.N), back ? n : d, raw);
+        } else {
+            st_pop<NT>(plane(f, I, g.N), d, raw);
         }
-        st_pop<NT>(plane(f, I, g.N), d, raw);
     }
 }
 
@@ -1473,11 +1474,19 @@ __device__ __forceinline__ void fused_body(P *__restrict__ f, const P4<T> *__res
 // Single-run kernels: workgroup w handles tile w of the run.
 //
 // Runs with solid cells: the solid-aware code (mask checks on every stencil and streaming
-// access) is needed only by tiles that have a solid cell within one cell (in any direction) of
-// one of their cells; every other tile takes the solid-free code, which evaluates the same
-// expressions.  tsolid[w] (k_tile_solid) tells which; null means every tile is solid-aware.
-__device__ __forceinline__ bool tile_free(const uint8_t *__restrict__ tsolid) {
-    return tsolid && !tsolid[blockIdx.x];
+// access) is needed only next to solids, and the rest takes the solid-free code, which evaluates
+// the same expressions.  Bit k of tsolid[w] (k_tile_solid) tells whether a solid cell lies within
+// one cell (in any direction) of a cell of wave k of tile w; null means everywhere.  The passes
+// choose per wave; those that stage porosity in LDS (STAGED, 16-bit storage) choose per tile, as
+// all waves of a tile then meet at a barrier.  In a duct with solid x faces every tile of a row of
+// 384 cells touches a solid, but only two of its six waves (384 x 192 x 192, FP32: swapped-phase
+// collision 1,044 -> 890 us with the address selects of load_raw and store_pop, natural 886 -> 880).
+template <bool STAGED>
+__device__ __forceinline__ bool solid_free(const uint8_t *__restrict__ tsolid) {
+    if (!tsolid) return false;
+    const uint32_t bits = tsolid[blockIdx.x];
+    if constexpr (STAGED) return bits == 0;
+    else return ((bits >> __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) & 1u) == 0;
 }
 
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
@@ -1491,7 +1500,7 @@ __global__ __launch_bounds__(256) void k_moments(const P *__restrict__ f,
                                                  P4<T> *__restrict__ m0_out, Grid g, Tiling tl,
                                                  Phys<T> ph) {
     if constexpr (SOLIDS) {
-        if (tile_free(tsolid)) {
+        if (solid_free<PopFmt<P>::shifted>(tsolid)) {
             moments_body<D, T, P, false, PH, AD>(f, eps, muD, muF, mask, m1_out, m0_out, g, tl,
                                                  ph, blockIdx.x);
             return;
@@ -1537,7 +1546,7 @@ __global__ __launch_bounds__(256) void k_vcorrect(const P4<T> *__restrict__ own_
         return;
     }
     if constexpr (SOLIDS) {
-        if (tile_free(tsolid)) {
+        if (solid_free<false>(tsolid)) {
             vcorrect_body<D, T, false, AD>(own_src, m1, eps, mask, m2_out, g, tl, ph, blockIdx.x);
             return;
         }
@@ -1572,7 +1581,7 @@ void k_collide(P *__restrict__ f, const P4<T> *__restrict__ m2, const P4<T> *__r
                const uint8_t *__restrict__ mask, const uint8_t *__restrict__ tsolid, Grid g,
                Tiling tl, Phys<T> ph) {
     if constexpr (SOLIDS) {
-        if (tile_free(tsolid)) {
+        if (solid_free<false>(tsolid)) {
             collide_body<D, T, P, false, PH, AD>(f, m2, nbr, eps, muD, muF, mask, g, tl, ph,
                                                  blockIdx.x);
             return;
@@ -1829,7 +1838,7 @@ void k_fused(P *__restrict__ f, const P4<T> *__restrict__ m1p, const P4<T> *__re
              const uint8_t *__restrict__ mask, const uint8_t *__restrict__ tsolid, Grid g,
              Tiling tl, Phys<T> ph) {
     if constexpr (SOLIDS) {
-        if (tile_free(tsolid)) {
+        if (solid_free<PopFmt<P>::shifted>(tsolid)) {
             fused_body<D, T, P, false, PH, AD>(f, m1p, m2p, m1n, m2n, eps, muD, muF, mask, g, tl,
                                                ph, blockIdx.x);
             return;
@@ -1839,8 +1848,8 @@ void k_fused(P *__restrict__ f, const P4<T> *__restrict__ m1p, const P4<T> *__re
                                         blockIdx.x);
 }
 
-// tsolid[w] = 1 when a cell of tile w, or a cell within one cell of one of them (faces, edges
-// and corners, through the periodic wrap), is solid.  Same grid and tile order as the passes;
+// Bit k of tsolid[w] = 1 when a cell of wave k (cells 64 k .. 64 k + 63) of tile w, or a cell within
+// one cell of one of them (faces, edges and corners, through the periodic wrap), is solid.  Same grid and tile order as the passes;
 // workgroups past the last tile write nothing (the passes return before reading theirs).
 template <int D>
 __global__ __launch_bounds__(256) void k_tile_solid(const uint8_t *__restrict__ mask, Grid g,
@@ -1857,8 +1866,12 @@ __global__ __launch_bounds__(256) void k_tile_solid(const uint8_t *__restrict__ 
             any |= mask[nb.at(Lat<D>::c[i][0], Lat<D>::c[i][1], Lat<D>::c[i][2])];
         });
     }
-    any = __syncthreads_or(any);
-    if (threadIdx.x == 0) tsolid[blockIdx.x] = any ? 1 : 0;
+    __shared__ uint32_t wave_any[4];
+    const unsigned long long lanes = __ballot(any != 0);
+    if ((threadIdx.x & 63u) == 0) wave_any[threadIdx.x >> 6] = lanes != 0;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        tsolid[blockIdx.x] = (uint8_t)(wave_any[0] | wave_any[1] << 1 | wave_any[2] << 2 | wave_any[3] << 3);
 }
 
 // tflat[w] = 1 when some cell of tile w has a porosity neighbourhood (the 3 x 3 (x 3) cells

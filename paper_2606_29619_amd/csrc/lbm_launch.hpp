@@ -144,13 +144,17 @@ lbm::BNodes<T> bnodes_of(const lbm_solver *h) {
                           ws_ptr<const lbm::P4<T>>(h, h->L.bval), h->nb};
 }
 
+inline dim3 bc_grid(const lbm_solver *h) {
+    return dim3((h->nb + lbm::kBcThreads - 1) / lbm::kBcThreads);
+}
+
 struct BcOutflowPass {
     static constexpr bool kDerivs = false;
     const lbm_solver *h;
     template <int D, typename T, typename P, bool S, int PH>
     void operator()() {
         if constexpr (S)
-            hipLaunchKernelGGL((lbm::k_bc_outflow<D, T, P, S, PH>), flat_grid(h->nb), dim3(256), 0,
+            hipLaunchKernelGGL((lbm::k_bc_outflow<D, T, P, S, PH>), bc_grid(h), dim3(lbm::kBcThreads), 0,
                                h->stream, ws_ptr<P>(h, f_off(h)), mask_ptr(h),
                                ws_ptr<const T>(h, h->L.eps), bnodes_of<T>(h), grid_of(h),
                                phys_of<T>(h));
@@ -164,7 +168,7 @@ struct BcRecordsPass {
     template <int D, typename T, typename P, bool S, int PH, bool AD>
     void operator()() {
         if constexpr (S)
-            hipLaunchKernelGGL((lbm::k_bc_records<D, T, P, S, PH, AD>), flat_grid(h->nb), dim3(256), 0,
+            hipLaunchKernelGGL((lbm::k_bc_records<D, T, P, S, PH, AD>), bc_grid(h), dim3(lbm::kBcThreads), 0,
                                h->stream, ws_ptr<const P>(h, f_off(h)), mask_ptr(h),
                                ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                                ws_ptr<const T>(h, h->L.muF), ws_ptr<lbm::P4<T>>(h, m1),
@@ -179,7 +183,7 @@ struct BcFixPass {
     template <int D, typename T, typename P, bool S, int PH>
     void operator()() {
         if constexpr (S)
-            hipLaunchKernelGGL((lbm::k_bc_fix<T>), flat_grid(h->nb), dim3(256), 0, h->stream,
+            hipLaunchKernelGGL((lbm::k_bc_fix<T>), bc_grid(h), dim3(lbm::kBcThreads), 0, h->stream,
                                ws_ptr<const lbm::P4<T>>(h, m1), ws_ptr<lbm::P4<T>>(h, m2),
                                bnodes_of<T>(h));
     }
@@ -191,7 +195,7 @@ struct BcRebuildPass {  // own records m2, stencil neighbours' nbr
     template <int D, typename T, typename P, bool S, int PH, bool AD>
     void operator()() {
         if constexpr (S)
-            hipLaunchKernelGGL((lbm::k_bc_rebuild<D, T, P, S, PH, AD>), flat_grid(h->nb), dim3(256), 0,
+            hipLaunchKernelGGL((lbm::k_bc_rebuild<D, T, P, S, PH, AD>), bc_grid(h), dim3(lbm::kBcThreads), 0,
                                h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                                ws_ptr<const lbm::P4<T>>(h, nbr),
                                ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
