@@ -145,19 +145,30 @@ int check_handle(const lbm_solver *h) {
     return LBM_OK;
 }
 
-// Packed-row tiles, unless the caller asks for rectangular tiles: always for FP32 / FP64
-// storage; for the 16-bit forms, whose moment and lagged passes then read the porosity of their
-// decode through the caches (the 26 neighbours of a D3Q27 cell) instead of from LDS, only on
-// D3Q27 runs whose rectangular tiles would leave at least 30 % of the lanes idle.  Measured on
-// the first 12 requests of the serving stream (FP16, packed against rectangular MLUPS): x
-// extents 81, 37, 159 (37-42 % idle) +8 %, +3 %, +12 %; 107, 125, 50 (2-22 % idle) -14 %,
-// -16 %, -10 %; D2Q9 rows of 291 and 350 cells (43 %, 32 %) -9 %, -4 %.
-bool packed_rows_ok(const lbm_params *p) {
-    if (p->tiles == LBM_TILES_RECTANGULAR) return false;
-    if (p->storage == LBM_F32 || p->storage == LBM_F64) return true;
-    const int tx = rect_tile_x(p->nx);
-    const int padded = (p->nx + tx - 1) / tx * tx;
-    return p->lattice == LBM_D3Q27 && 10 * (padded - p->nx) >= 3 * padded;
+// Tiles of a run.  FP32 and FP64 storage: packed rows for x extents that are not a multiple of 64,
+// in every pass, unless the caller asks for rectangular tiles.
+// 16-bit storage: the moment and lagged passes read the porosity of their decode (the 26 neighbours of
+// a D3Q27 cell) from LDS, staged for a rectangular tile, and take the narrowest tile, whose halo is the
+// smallest (64 x 4: 1,188 values, 256 x 1: 2,322; 256 x 192 x 192 FP16 moment pass 161 against 184 us,
+// 192^3 BF16 lagged pass 376 against 455 us); the collision stages nothing and, on D3Q27, takes packed
+// rows like FP32's.  FP16 150^3, moment and collision pass: packed 123 + 145 us, rectangular 64 x 4
+// 76 + 180 us; 200^3 275 + 306 and 158 + 469 us.  With solids the passes share one set of tile flags
+// and so one kind of tile: packed where a D3Q27 run's rectangular tiles would leave at least 30 % of
+// the lanes idle.
+RunTiles run_tiles(const lbm_params *p) {
+    const int nx = p->nx, ny = p->ny, nz = p->nz, tx = rect_tile_x(nx);
+    const bool ragged = nx % 64 != 0 && p->tiles != LBM_TILES_RECTANGULAR;
+    if (p->storage == LBM_F32 || p->storage == LBM_F64) {
+        const lbm::Tiling t = make_tiling(nx, ny, nz, ragged, tx);
+        return {t, t};
+    }
+    const bool d3 = p->lattice == LBM_D3Q27;
+    if (p->mask) {
+        const int padded = (nx + tx - 1) / tx * tx;
+        const lbm::Tiling t = make_tiling(nx, ny, nz, ragged && d3 && 10 * (padded - nx) >= 3 * padded, tx);
+        return {t, t};
+    }
+    return {make_tiling(nx, ny, nz, ragged && d3, tx), make_tiling(nx, ny, nz, false, 64)};
 }
 
 // Whole step in one launch (k_plane_step), from one population buffer into another: every
@@ -355,7 +366,7 @@ int run_layout(const lbm_params *p, Layout *L) {
     bool bo, bv, bvisc;
     rc = boundary_nodes(p, D, N, &nb, &bo, &bv, &bvisc);
     if (rc) return rc;
-    const lbm::Tiling tl = make_tiling(p->nx, p->ny, p->nz, packed_rows_ok(p));
+    const lbm::Tiling tl = run_tiles(p).cells;
     *L = make_layout(Q, D, (size_t)N, sp, s, p->mask != nullptr, p->scheme == LBM_SCHEME_LAGGED,
                      8 * (size_t)tl.per, nb, p->picard_iters > 0, p->grad_eps != nullptr,
                      plane_step_ok(p, nb));
@@ -450,7 +461,8 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     bool bc_outflow = false, bc_vp = false, bc_visc = false;
     rc = boundary_nodes(p, D, N, &nb, &bc_outflow, &bc_vp, &bc_visc);
     if (rc) return rc;
-    const lbm::Tiling tiles = make_tiling(p->nx, p->ny, p->nz, packed_rows_ok(p));
+    const RunTiles rt = run_tiles(p);
+    const lbm::Tiling &tiles = rt.cells;
     const Layout L = make_layout(Q, D, (size_t)N, sp, s, solids, p->scheme == LBM_SCHEME_LAGGED,
                                  8 * (size_t)tiles.per, nb, p->picard_iters > 0,
                                  p->grad_eps != nullptr, plane_step_ok(p, nb));
@@ -474,7 +486,8 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->stream = reinterpret_cast<hipStream_t>(hip_stream);
     h->ws = reinterpret_cast<char *>(dev_workspace);
     h->L = L;
-    h->tiles = tiles;
+    h->tiles = rt.cells;
+    h->mtiles = rt.moments;
     h->step = 0;
     h->phase = 0;
     h->scheme = p->scheme;
@@ -543,8 +556,8 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
         // padding workgroups past the last tile write no flag
         if ((e = hipMemsetAsync(ts, 0, 8 * (size_t)h->tiles.per, h->stream)) != hipSuccess)
             return cleanup(fail(LBM_ERR_HIP, "tile-flag clear failed: %s", hipGetErrorString(e)));
-        if (D == 2) hipLaunchKernelGGL(lbm::k_tile_solid<2>, cell_tiles(h), dim3(256), 0, h->stream, mask_ptr(h), grid_of(h), h->tiles, ts);
-        else hipLaunchKernelGGL(lbm::k_tile_solid<3>, cell_tiles(h), dim3(256), 0, h->stream, mask_ptr(h), grid_of(h), h->tiles, ts);
+        if (D == 2) hipLaunchKernelGGL(lbm::k_tile_solid<2>, tile_grid(h->tiles), dim3(256), 0, h->stream, mask_ptr(h), grid_of(h), h->tiles, ts);
+        else hipLaunchKernelGGL(lbm::k_tile_solid<3>, tile_grid(h->tiles), dim3(256), 0, h->stream, mask_ptr(h), grid_of(h), h->tiles, ts);
         if ((e = hipGetLastError()) != hipSuccess)
             return cleanup(fail(LBM_ERR_HIP, "tile-flag kernel failed: %s", hipGetErrorString(e)));
     }
@@ -559,11 +572,11 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     if (!h->analytic) {  // after the static-field kernel has written eps (same stream)
         uint8_t *tf = reinterpret_cast<uint8_t *>(h->ws + L.tflat);
         if (h->storage == LBM_F64) {
-            if (D == 2) hipLaunchKernelGGL((lbm::k_tile_flat<2, double>), cell_tiles(h), dim3(256), 0, h->stream, ws_ptr<const double>(h, L.eps), grid_of(h), h->tiles, tf);
-            else hipLaunchKernelGGL((lbm::k_tile_flat<3, double>), cell_tiles(h), dim3(256), 0, h->stream, ws_ptr<const double>(h, L.eps), grid_of(h), h->tiles, tf);
+            if (D == 2) hipLaunchKernelGGL((lbm::k_tile_flat<2, double>), tile_grid(h->tiles), dim3(256), 0, h->stream, ws_ptr<const double>(h, L.eps), grid_of(h), h->tiles, tf);
+            else hipLaunchKernelGGL((lbm::k_tile_flat<3, double>), tile_grid(h->tiles), dim3(256), 0, h->stream, ws_ptr<const double>(h, L.eps), grid_of(h), h->tiles, tf);
         } else {
-            if (D == 2) hipLaunchKernelGGL((lbm::k_tile_flat<2, float>), cell_tiles(h), dim3(256), 0, h->stream, ws_ptr<const float>(h, L.eps), grid_of(h), h->tiles, tf);
-            else hipLaunchKernelGGL((lbm::k_tile_flat<3, float>), cell_tiles(h), dim3(256), 0, h->stream, ws_ptr<const float>(h, L.eps), grid_of(h), h->tiles, tf);
+            if (D == 2) hipLaunchKernelGGL((lbm::k_tile_flat<2, float>), tile_grid(h->tiles), dim3(256), 0, h->stream, ws_ptr<const float>(h, L.eps), grid_of(h), h->tiles, tf);
+            else hipLaunchKernelGGL((lbm::k_tile_flat<3, float>), tile_grid(h->tiles), dim3(256), 0, h->stream, ws_ptr<const float>(h, L.eps), grid_of(h), h->tiles, tf);
         }
         if ((e = hipGetLastError()) != hipSuccess)
             return cleanup(fail(LBM_ERR_HIP, "flat-tile kernel failed: %s", hipGetErrorString(e)));

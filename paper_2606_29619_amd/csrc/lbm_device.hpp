@@ -985,6 +985,31 @@ struct Tiling {
     uint64_t mnx;     // ceil(2^64 / nx): p / nx = umulhi64(p, mnx) for p < 2^32, nx >= 2
 };
 
+// Blocks of tile rows (64 along y, 4 along z: measured best on 256^3) and tiles per XCD.
+__host__ __device__ inline void block_tiles(Tiling &t, int nz) {
+    t.ntz = nz;
+    t.by = t.nty < 64 ? t.nty : 64;
+    t.bz = nz < 4 ? nz : 4;
+    t.nby = (t.nty + t.by - 1) / t.by;
+    t.nbz = (nz + t.bz - 1) / t.bz;
+    t.per = (uint32_t)(((int64_t)t.ntx * t.by * t.bz * t.nby * t.nbz + 7) / 8);
+}
+
+// Packed-row tiles of a grid; mnx: see Tiling.
+__host__ __device__ inline Tiling packed_tiling(int nx, int ny, int nz, uint64_t mnx) {
+    Tiling t{};
+    t.packed = 1;
+    t.tx = 256;
+    t.ltx = 8;
+    t.ty = 1;
+    t.ntx = 1;
+    t.pn = (uint32_t)nx * (uint32_t)ny;
+    t.nty = (int)((t.pn + 255u) / 256u);
+    t.mnx = mnx;
+    block_tiles(t, nz);
+    return t;
+}
+
 // Cell of this thread in tile w: returns -1 when the whole tile lies outside the order (the
 // same for every thread of the workgroup), 0 when the thread's cell is outside the grid (ragged
 // edge), 1 otherwise; (x0, y0) is the tile origin.

@@ -127,7 +127,8 @@ struct lbm_solver {
     int picard_iters;
     double picard_omega;
     bool analytic;      // analytic porosity derivatives in L.deps
-    lbm::Tiling tiles;  // 256-cell tiles, blocked, in XCD-contiguous ranges
+    lbm::Tiling tiles;  // 256-cell tiles, blocked, in XCD-contiguous ranges: collision and others
+    lbm::Tiling mtiles; // the same of the moment and lagged passes (see run_tiles)
     bool fused_vc;      // velocity correction inside the collision pass (k_collide_vc)
     bool plane_step;    // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
     bool solid_occ;     // runs with solids: under a quarter of the tiles solid-aware
@@ -206,42 +207,40 @@ inline lbm::ZTiling make_ztiling(int nx, int ny, int nz, int tx, int ty) {
     return z;
 }
 
-// Tiles of the cell passes.  Rectangular tiles (256 x 1, 128 x 2 or 64 x 4 cells) when the x
-// extent is a multiple of 64 (or the caller asks for them); packed rows otherwise, so that rows
-// of, say, 70 cells do not leave most of a second wave idle.
-// Width of the rectangular row tiles for an x extent nx.
-inline int rect_tile_x(int nx) { return nx >= 192 ? 256 : (nx >= 96 ? 128 : 64); }
-
-inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed_ok = false) {
-    lbm::Tiling t{};
-    if (packed_ok && nx % 64 != 0) {
-        t.packed = 1;
-        t.tx = 256;
-        t.ltx = 8;
-        t.ty = 1;
-        t.ntx = 1;
-        t.pn = (uint32_t)nx * (uint32_t)ny;
-        t.nty = (int)((t.pn + 255u) / 256u);
-        t.mnx = nx >= 2 ? ~uint64_t(0) / (uint64_t)nx + 1 : 0;
-    } else {
-        t.tx = rect_tile_x(nx);
-        t.ltx = t.tx == 256 ? 8 : (t.tx == 128 ? 7 : 6);
-        t.ty = 256 / t.tx;
-        t.ntx = (nx + t.tx - 1) / t.tx;
-        t.nty = (ny + t.ty - 1) / t.ty;
+// Width of the rectangular row tiles (256 x 1, 128 x 2 or 64 x 4 cells) for an x extent nx: the one
+// that leaves the fewest lanes past the row's end, a wider tile being worth 3 % of padding per
+// doubling (fewer tile edges in x).  us per step of the separate FP32 passes at widths 64 / 128 /
+// 256: 320 x 192 x 150 823 / 828 / 1,023; 384 x 192 x 192 1,280 / 1,251 / 1,443; 448 x 160 x 100
+// 617 / 659 / 650; 256 x 192 x 192 869 / 857 / 827; FP64 192^3 1,319 / 1,507 / 1,340.
+inline int rect_tile_x(int nx) {
+    int best = 256;
+    int64_t cost = INT64_MAX;
+    for (int tx = 256, pct = 100; tx >= 64; tx /= 2, pct += 3) {
+        const int64_t c = (int64_t)((nx + tx - 1) / tx) * tx * pct;
+        if (c < cost) {
+            cost = c;
+            best = tx;
+        }
     }
-    t.ntz = nz;
-    const int by = 64, bz = 4;  // tile rows per block along y and z (measured best on 256^3)
-    t.by = std::min(by, t.nty);
-    t.bz = std::min(bz, t.ntz);
-    t.nby = (t.nty + t.by - 1) / t.by;
-    t.nbz = (t.ntz + t.bz - 1) / t.bz;
-    const int64_t nt = (int64_t)t.ntx * t.by * t.bz * t.nby * t.nbz;
-    t.per = (uint32_t)((nt + 7) / 8);
+    return best;
+}
+
+// Tiles of the cell passes: rectangular tiles of tx cells along x, or packed rows, so that rows of,
+// say, 70 cells do not leave most of a second wave idle.
+inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
+    if (packed) return lbm::packed_tiling(nx, ny, nz, nx >= 2 ? ~uint64_t(0) / (uint64_t)nx + 1 : 0);
+    lbm::Tiling t{};
+    t.tx = tx;
+    t.ltx = t.tx == 256 ? 8 : (t.tx == 128 ? 7 : 6);
+    t.ty = 256 / t.tx;
+    t.ntx = (nx + t.tx - 1) / t.tx;
+    t.nty = (ny + t.ty - 1) / t.ty;
+    lbm::block_tiles(t, nz);
     return t;
 }
 
-inline dim3 cell_tiles(const lbm_solver *h) { return dim3((unsigned)(8 * (int64_t)h->tiles.per)); }
+// Grid of a cell pass: workgroups of one tile, padded to the same number on each XCD.
+inline dim3 tile_grid(const lbm::Tiling &t) { return dim3((unsigned)(8 * (int64_t)t.per)); }
 
 template <typename T>
 T *ws_ptr(const lbm_solver *h, size_t off) {
@@ -263,6 +262,13 @@ inline const uint8_t *tsolid_ptr(const lbm_solver *h) {
 inline const uint8_t *tflat_ptr(const lbm_solver *h) {
     return h->analytic ? nullptr : reinterpret_cast<const uint8_t *>(h->ws + h->L.tflat);
 }
+
+// Tiles of a run's passes.
+struct RunTiles {
+    lbm::Tiling cells;    // collision, velocity correction and the passes at creation and reading
+    lbm::Tiling moments;  // moment and lagged passes
+};
+RunTiles run_tiles(const lbm_params *p);
 
 // Workspace layout of a run with the shape and options of p (validates them; host only).
 int run_layout(const lbm_params *p, Layout *L);

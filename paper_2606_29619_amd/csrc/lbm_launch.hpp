@@ -19,16 +19,16 @@ template <int D, typename T, typename P, bool S, int PH, bool AD>
 void launch_moments(const lbm_solver *h, size_t m1_out) {
     auto ph = phys_of<T>(h);
     lbm::P4<T> *m0 = h->picard_iters ? ws_ptr<lbm::P4<T>>(h, h->L.m0) : nullptr;
-    hipLaunchKernelGGL((lbm::k_moments<D, T, P, S, PH, AD>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_moments<D, T, P, S, PH, AD>), tile_grid(h->mtiles), dim3(256), 0, h->stream,
                        ws_ptr<const P>(h, f_off(h)), ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
-                       tsolid_ptr(h), ws_ptr<lbm::P4<T>>(h, m1_out), m0, grid_of(h), h->tiles, ph);
+                       tsolid_ptr(h), ws_ptr<lbm::P4<T>>(h, m1_out), m0, grid_of(h), h->mtiles, ph);
 }
 
 template <int D, typename T, bool S, bool AD>
 void launch_picard(const lbm_solver *h, size_t vin, size_t vout) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_picard<D, T, S, AD>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_picard<D, T, S, AD>), tile_grid(h->tiles), dim3(256), 0, h->stream,
                        ws_ptr<const lbm::P4<T>>(h, vin), ws_ptr<const lbm::P4<T>>(h, h->L.m0),
                        ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                        ws_ptr<const T>(h, h->L.muF), mask_ptr(h), ws_ptr<lbm::P4<T>>(h, vout),
@@ -38,7 +38,7 @@ void launch_picard(const lbm_solver *h, size_t vin, size_t vout) {
 template <int D, typename T, bool S, bool AD>
 void launch_vcorrect(const lbm_solver *h, size_t own_src, size_t m1, size_t m2_out) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_vcorrect<D, T, S, AD>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_vcorrect<D, T, S, AD>), tile_grid(h->tiles), dim3(256), 0, h->stream,
                        ws_ptr<const lbm::P4<T>>(h, own_src), ws_ptr<const lbm::P4<T>>(h, m1),
                        ws_ptr<const T>(h, h->L.eps), mask_ptr(h), tsolid_ptr(h), tflat_ptr(h),
                        ws_ptr<lbm::P4<T>>(h, m2_out), grid_of(h), h->tiles, ph);
@@ -47,7 +47,7 @@ void launch_vcorrect(const lbm_solver *h, size_t own_src, size_t m1, size_t m2_o
 template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
 void launch_collide_occ(const lbm_solver *h, size_t m2, size_t nbr) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_collide<D, T, P, S, PH, AD, OCC>), cell_tiles(h), dim3(256), 0,
+    hipLaunchKernelGGL((lbm::k_collide<D, T, P, S, PH, AD, OCC>), tile_grid(h->tiles), dim3(256), 0,
                        h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                        ws_ptr<const lbm::P4<T>>(h, nbr),
                        ws_ptr<const T>(h, h->L.eps),
@@ -80,13 +80,13 @@ void launch_collide_vc(const lbm_solver *h, size_t m1) {
 template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
 void launch_fused_occ(const lbm_solver *h, int prev, int next) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_fused<D, T, P, S, PH, AD, OCC>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_fused<D, T, P, S, PH, AD, OCC>), tile_grid(h->mtiles), dim3(256), 0, h->stream,
                        ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, h->L.m1[prev]),
                        ws_ptr<const lbm::P4<T>>(h, h->L.m2[prev]),
                        ws_ptr<lbm::P4<T>>(h, h->L.m1[next]), ws_ptr<lbm::P4<T>>(h, h->L.m2[next]),
                        ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
                        ws_ptr<const T>(h, h->L.muF), mask_ptr(h), tsolid_ptr(h), grid_of(h),
-                       h->tiles, ph);
+                       h->mtiles, ph);
 }
 
 template <int D, typename T, typename P, bool S, int PH, bool AD>
@@ -103,7 +103,7 @@ void launch_fused(const lbm_solver *h, int prev, int next) {
 template <int D, typename T, typename P, bool S, bool AD>
 void launch_init(const lbm_solver *h) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_init<D, T, P, S, AD>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_init<D, T, P, S, AD>), tile_grid(h->tiles), dim3(256), 0, h->stream,
                        ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, h->L.m2[0]),
                        ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
@@ -112,14 +112,14 @@ void launch_init(const lbm_solver *h) {
 
 template <int D, typename T, typename P, bool S, int PH, typename O>
 void launch_export(const lbm_solver *h, O *out) {
-    hipLaunchKernelGGL((lbm::k_export<D, T, P, S, PH, O>), cell_tiles(h), dim3(256), 0,
+    hipLaunchKernelGGL((lbm::k_export<D, T, P, S, PH, O>), tile_grid(h->tiles), dim3(256), 0,
                        h->stream, ws_ptr<const P>(h, f_off(h)), mask_ptr(h),
                        ws_ptr<const T>(h, h->L.eps), out, grid_of(h), h->tiles, phys_of<T>(h));
 }
 
 template <int D, typename T, typename P, bool S, typename I>
 void launch_import(const lbm_solver *h, const I *in) {
-    hipLaunchKernelGGL((lbm::k_import<D, T, P, S, I>), cell_tiles(h), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_import<D, T, P, S, I>), tile_grid(h->tiles), dim3(256), 0, h->stream,
                        ws_ptr<P>(h, f_off(h)), in, mask_ptr(h), ws_ptr<const T>(h, h->L.eps),
                        grid_of(h), h->tiles, phys_of<T>(h));
 }

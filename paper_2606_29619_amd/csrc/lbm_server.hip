@@ -33,10 +33,17 @@ struct RunDesc {
     P4<T> *m1[2];
     P4<T> *m2[2];
     Grid g;
-    Tiling tl;
+    Tiling tl;   // tiles of the moment and lagged passes
     Phys<T> ph;
-    int cur;  // record pair holding the previous step's moments at the start of the round
+    int cur;     // record pair holding the previous step's moments at the start of the round
+    int packed;  // the correction and the collision take packed rows while tl is rectangular
+                 // (tl.mnx is set for them)
 };
+
+template <typename T, typename P>
+__device__ __forceinline__ Tiling cells_of(const RunDesc<T, P> &d) {
+    return d.packed ? packed_tiling(d.g.nx, d.g.ny, d.g.nz, d.tl.mnx) : d.tl;
+}
 
 __device__ __forceinline__ int find_run(const uint32_t *__restrict__ starts, int nrun,
                                         uint32_t w) {
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(256) void kb_vcorrect(const RunDesc<T, P> *__restri
                                                    const uint32_t *__restrict__ starts, int nrun) {
     const int r = find_run(starts, nrun, blockIdx.x);
     const RunDesc<T, P> &d = runs[r];
-    vcorrect_body<D, T, S, false>(d.m1[0], d.m1[0], d.eps, d.mask, d.m2[0], d.g, d.tl, d.ph,
+    vcorrect_body<D, T, S, false>(d.m1[0], d.m1[0], d.eps, d.mask, d.m2[0], d.g, cells_of(d), d.ph,
                            blockIdx.x - starts[r]);
 }
 
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(256) void kb_collide(const RunDesc<T, P> *__restric
     const int r = find_run(starts, nrun, blockIdx.x);
     const RunDesc<T, P> &d = runs[r];
     collide_body<D, T, P, S, PH, false>(d.f, d.m2[0], d.m2[0], d.eps, d.muD, d.muF, d.mask, d.g,
-                                        d.tl, d.ph, blockIdx.x - starts[r]);
+                                        cells_of(d), d.ph, blockIdx.x - starts[r]);
 }
 
 // parity: the step's position in the round (mod 2); the previous records alternate with it.
@@ -166,7 +173,7 @@ struct Request {
 
 constexpr int kMaxRuns = 4096;
 constexpr int kStarvationRounds = 64;
-// descriptor table: the largest descriptor per run plus one start index per run and group
+// descriptor table: the largest descriptor and two start indices per run
 constexpr size_t kTableBytes =
     (size_t)kMaxRuns * (sizeof(lbm::RunDesc<double, double>) + 2 * sizeof(uint32_t)) + 64 * 1024;
 
@@ -203,8 +210,9 @@ struct Group {
     int D, storage, scheme;
     bool solids;
     std::vector<lbmh::Request *> runs;
-    size_t desc_off = 0, starts_off = 0;  // device offsets in the pool
-    uint32_t nwg = 0;
+    // device offsets in the pool; starts of the moment and lagged passes, and of the others
+    size_t desc_off = 0, starts_off = 0, cstarts_off = 0;
+    uint32_t nwg = 0, cnwg = 0;
 };
 
 template <int D, typename T, typename P, bool S>
@@ -216,8 +224,8 @@ struct GroupOps {
         size_t at = align256(tab.size());
         gr.desc_off = sv->table_off + at;
         tab.resize(at + gr.runs.size() * sizeof(Desc));
-        uint32_t wg = 0;
-        std::vector<uint32_t> starts;
+        uint32_t wg = 0, cwg = 0;
+        std::vector<uint32_t> starts, cstarts;
         for (size_t k = 0; k < gr.runs.size(); ++k) {
             const lbm_solver *h = gr.runs[k]->h;
             Desc d;
@@ -231,24 +239,34 @@ struct GroupOps {
                 d.m2[j] = ws_ptr<lbm::P4<T>>(h, h->L.m2[j]);
             }
             d.g = grid_of(h);
-            d.tl = h->tiles;
+            d.tl = h->mtiles;
+            d.packed = h->tiles.packed && !h->mtiles.packed;
+            if (d.packed) d.tl.mnx = h->tiles.mnx;
             d.ph = phys_of<T>(h);
             d.cur = h->cur;
             std::memcpy(tab.data() + at + k * sizeof(Desc), &d, sizeof(Desc));
             starts.push_back(wg);
-            wg += 8u * h->tiles.per;
+            wg += 8u * d.tl.per;
+            cstarts.push_back(cwg);
+            cwg += 8u * (d.packed ? h->tiles.per : d.tl.per);
         }
         gr.nwg = wg;
+        gr.cnwg = cwg;
         at = align256(tab.size());
         gr.starts_off = sv->table_off + at;
         tab.resize(at + starts.size() * sizeof(uint32_t));
         std::memcpy(tab.data() + at, starts.data(), starts.size() * sizeof(uint32_t));
+        at = align256(tab.size());
+        gr.cstarts_off = sv->table_off + at;
+        tab.resize(at + cstarts.size() * sizeof(uint32_t));
+        std::memcpy(tab.data() + at, cstarts.data(), cstarts.size() * sizeof(uint32_t));
     }
 
     template <int PH>
     static void step_ph(lbm_server *sv, const Group &gr, int parity) {
         const Desc *runs = reinterpret_cast<const Desc *>(sv->pool + gr.desc_off);
         const uint32_t *starts = reinterpret_cast<const uint32_t *>(sv->pool + gr.starts_off);
+        const uint32_t *cstarts = reinterpret_cast<const uint32_t *>(sv->pool + gr.cstarts_off);
         const int n = (int)gr.runs.size();
         if (gr.scheme == LBM_SCHEME_LAGGED) {
             hipLaunchKernelGGL((lbm::kb_fused<D, T, P, S, PH>), dim3(gr.nwg), dim3(256), 0,
@@ -256,10 +274,10 @@ struct GroupOps {
         } else {
             hipLaunchKernelGGL((lbm::kb_moments<D, T, P, S, PH>), dim3(gr.nwg), dim3(256), 0,
                                sv->stream, runs, starts, n);
-            hipLaunchKernelGGL((lbm::kb_vcorrect<D, T, P, S>), dim3(gr.nwg), dim3(256), 0,
-                               sv->stream, runs, starts, n);
-            hipLaunchKernelGGL((lbm::kb_collide<D, T, P, S, PH>), dim3(gr.nwg), dim3(256), 0,
-                               sv->stream, runs, starts, n);
+            hipLaunchKernelGGL((lbm::kb_vcorrect<D, T, P, S>), dim3(gr.cnwg), dim3(256), 0,
+                               sv->stream, runs, cstarts, n);
+            hipLaunchKernelGGL((lbm::kb_collide<D, T, P, S, PH>), dim3(gr.cnwg), dim3(256), 0,
+                               sv->stream, runs, cstarts, n);
         }
     }
 
