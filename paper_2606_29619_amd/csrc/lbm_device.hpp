@@ -87,7 +87,7 @@ struct Phys {
     T rho0;        // reference density of the 16-bit population shift
     int nu_pow;    // -1, 0, 1
     int eta_on;    // Phi^eta switched on
-    int shift_porous;  // 16-bit shift base rho0 eps(src) (1) or rho0 (0)
+    float shift_a, shift_b;  // 16-bit shift base shift_a eps(src) + shift_b: rho0 eps(src) or rho0
     const T *deps;     // analytic porosity derivatives: planes of dN values, grad eps (D planes)
                        // then the Hessian's upper triangle row by row; null: central differences
     uint32_t dN;       // plane stride of deps (cells)
@@ -107,6 +107,12 @@ __device__ __forceinline__ float dv(float a, float b) { return a * __builtin_amd
 // mass steadily with it).
 __device__ __forceinline__ double div_rn(double a, double b) { return a / b; }
 __device__ __forceinline__ float div_rn(float a, float b) { return a / b; }
+// a b + c where the product is exact (a power of two, or a sum with an exact zero): the fused form
+// then rounds as the two operations do.
+__device__ __forceinline__ double mad_exact(double a, double b, double c) { return a * b + c; }
+__device__ __forceinline__ float mad_exact(float a, float b, float c) {
+    return __builtin_fmaf(a, b, c);
+}
 __device__ __forceinline__ double sq(double x) { return sqrt(x); }
 __device__ __forceinline__ float sq(float x) { return __builtin_amdgcn_sqrtf(x); }
 
@@ -358,6 +364,12 @@ __device__ __forceinline__ constexpr float enc_scale() {
     return p;
 }
 
+// Shift base of a cell of porosity e: rho0 e (porous shift) or rho0, in one instruction.
+template <typename T>
+__device__ __forceinline__ float shift_base(T e, const Phys<T> &ph) {
+    return __builtin_fmaf(ph.shift_a, (float)e, ph.shift_b);
+}
+
 // Shift sigma_I = base * w_I of a value produced by a cell of porosity e_src (16-bit formats;
 // FP32 product).
 template <int D, int I, typename P, typename T>
@@ -365,19 +377,23 @@ __device__ __forceinline__ float shift_sigma(T e_src, const Phys<T> &ph) {
     if constexpr (!PopFmt<P>::shifted) {
         return 0.0f;
     } else {
-        const float base = ph.shift_porous ? ph.rho0 * e_src : ph.rho0;
-        return base * weight<D, I>();
+        return shift_base(e_src, ph) * weight<D, I>();
     }
 }
 
-// Value of a slot in arithmetic type A (FP32 in the kernels; FP64 for exact checkpoints).
+// Value of a slot in arithmetic type A (FP32 in the kernels; FP64 for exact checkpoints).  Decode
+// and encode take 4 and 3 instructions per population (base, sigma, conversion, scaled sum) where
+// the unfused forms with a select of the shift rule took 6 and 4, of about 950 in the collision, 420
+// in the moment pass: the 16-bit passes are bound by vector issue as much as by memory.  256^3 FP16
+// fused collision 706 -> 678 us, 224^3 BF16 lagged pass 673 -> 618 us, FP16 200 x 100 x 100 duct step
+// 399 -> 294 us.
 template <int D, int I, typename A, typename P>
 __device__ __forceinline__ A decode(P raw, float sigma) {
     if constexpr (!PopFmt<P>::shifted) {
         return (A)raw;
     } else {
         constexpr float dscale = 1.0f / enc_scale<D, I>();
-        return (A)sigma + (A)PopFmt<P>::dec(raw) * (A)dscale;
+        return mad_exact((A)PopFmt<P>::dec(raw), (A)dscale, (A)sigma);
     }
 }
 template <int D, int I, typename P, typename A>
@@ -386,7 +402,7 @@ __device__ __forceinline__ P encode(A v, float sigma) {
         return (P)v;
     } else {
         constexpr float escale = enc_scale<D, I>();
-        return PopFmt<P>::enc((float)((v - (A)sigma) * (A)escale));
+        return PopFmt<P>::enc((float)mad_exact(v, (A)escale, -((A)sigma * (A)escale)));
     }
 }
 
@@ -440,7 +456,6 @@ __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, co
     } else {
         using L = Lat<D>;
         constexpr int cx = L::c[I][0], cy = L::c[I][1], cz = L::c[I][2];
-        if (!ph.shift_porous) return shift_sigma<D, I, P>(T(1), ph);
         T e = ev.at(-cx, -cy, -cz);
         if constexpr (SOLIDS && (cx != 0 || cy != 0 || cz != 0)) {
             const T e0 = ev.at(0, 0, 0);
@@ -485,7 +500,7 @@ __device__ __forceinline__ void store_pop(P *__restrict__ f, const uint8_t *__re
 template <typename P, typename T>
 __device__ __forceinline__ float own_base(T e0, const Phys<T> &ph) {
     if constexpr (!PopFmt<P>::shifted) return 0.0f;
-    else return ph.shift_porous ? ph.rho0 * e0 : ph.rho0;
+    else return shift_base(e0, ph);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1252,7 +1267,10 @@ __device__ __forceinline__ void load_pair_group(const P *__restrict__ f,
 // fused correction-collision kernel 0.885 -> 0.846 ms, FP64 2.05 -> 1.96 ms; the 16-bit forms
 // load, decode, collide and store one group after the other (pipelined, their fused kernel
 // spills: 0.75 -> 0.83 ms).
-template <int D, typename T, typename P, bool SOLIDS, int PH, int FIRST = 0, typename E>
+// WEIGHTS: 16-bit storage under the lattice-weight shift, known at compile time, reads no porosity to
+// decode (every sigma is a constant); false serves both shift rules.
+template <int D, typename T, typename P, bool SOLIDS, int PH, int FIRST = 0, bool WEIGHTS = false,
+          typename E>
 __device__ __forceinline__ void collide_populations(P *__restrict__ f,
                                                     const uint8_t *__restrict__ mask,
                                                     const Grid &g, const Phys<T> &ph,
@@ -1264,7 +1282,7 @@ __device__ __forceinline__ void collide_populations(P *__restrict__ f,
     __builtin_amdgcn_sched_barrier(0);
     const T two_beta = T(2) * beta;
     const T omb = T(1) - beta;
-    const float base = own_base<P>(ev.at(0, 0, 0), ph);
+    const float base = WEIGHTS ? ph.shift_b : own_base<P>(ev.at(0, 0, 0), ph);
     // Swapped phase: population addresses recomputed from an opaque copy of the neighbourhood
     // (16-bit storage 0.76 -> 0.68 ms on the 256^3 box, FP64 2 % faster).  FP32 storage keeps
     // the addresses of the stencil loads: 7 instead of 4 waves per SIMD left its collision as
@@ -1298,8 +1316,9 @@ __device__ __forceinline__ void collide_populations(P *__restrict__ f,
             T fi[g1 - g0];
             unroll<g0, g1>([&](auto ii) {
                 constexpr int i = decltype(ii)::value;
-                fi[i - g0] = decode<D, i, T>(raw[i - g0],
-                                             load_sigma<D, SOLIDS, i, P>(mask, ev, ph, nbp));
+                fi[i - g0] = decode<D, i, T>(
+                    raw[i - g0], WEIGHTS ? base * weight<D, i>()
+                                         : load_sigma<D, SOLIDS, i, P>(mask, ev, ph, nbp));
             });
             unroll<g0, g1>([&](auto ii) {
                 constexpr int i = decltype(ii)::value;
@@ -1675,7 +1694,10 @@ struct EpsRing {
     }
 };
 
-template <typename T, typename PS, int PH>
+// WEIGHTS: see collide_populations; an instantiation of its own for that rule (256^3 FP16 box, fused
+// kernel: porous shift 678 us; lattice-weight shift 640 us, 679 us through the common form; both
+// rules in one kernel, chosen at run time, 728 and 707 us).
+template <typename T, typename PS, int PH, bool WEIGHTS>
 __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__restrict__ f,
                                                           const P4<T> *__restrict__ m1,
                                                           const T *__restrict__ eps,
@@ -1847,7 +1869,7 @@ __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__re
             const T er = own.e * own.r;
             peq.init(er, xi, P);
             pst.init(er, xs, Ps);
-            collide_populations<D, T, PS, false, PH, (PopFmt<PS>::shifted ? 0 : 1)>(
+            collide_populations<D, T, PS, false, PH, (PopFmt<PS>::shifted ? 0 : 1), WEIGHTS>(
                 f, nullptr, g, ph, ev, nb, cs.vs.beta, peq, pst, fa);
         }
         __syncthreads();

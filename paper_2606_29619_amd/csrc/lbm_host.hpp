@@ -166,7 +166,8 @@ lbm::Phys<T> phys_of(const lbm_solver *h) {
     for (int a = 0; a < 3; ++a) ph.b[a] = (T)h->b[a];
     ph.nu_pow = h->nu_eff_pow;
     ph.rho0 = (T)h->rho0;
-    ph.shift_porous = h->shift == LBM_SHIFT_POROUS ? 1 : 0;
+    ph.shift_a = h->shift == LBM_SHIFT_POROUS ? (float)h->rho0 : 0.0f;
+    ph.shift_b = h->shift == LBM_SHIFT_POROUS ? 0.0f : (float)h->rho0;
     ph.deps = h->analytic ? reinterpret_cast<const T *>(h->ws + h->L.deps) : nullptr;
     ph.dN = (uint32_t)h->N;
     return ph;

@@ -68,13 +68,26 @@ void launch_collide(const lbm_solver *h, size_t m2, size_t nbr) {
     launch_collide_occ<D, T, P, S, PH, AD, false>(h, m2, nbr);
 }
 
+template <typename T, typename P, int PH, bool WEIGHTS>
+void launch_collide_vc_shift(const lbm_solver *h, size_t m1) {
+    hipLaunchKernelGGL((lbm::k_collide_vc<T, P, PH, WEIGHTS>), dim3(8 * h->ztiles.per),
+                       dim3(lbm::ZCfg<T, P>::kThreads), 0, h->stream, ws_ptr<P>(h, f_off(h)),
+                       ws_ptr<const lbm::P4<T>>(h, m1), ws_ptr<const T>(h, h->L.eps),
+                       ws_ptr<const T>(h, h->L.muD),
+                       ws_ptr<const T>(h, h->L.muF), grid_of(h), h->ztiles, phys_of<T>(h));
+}
+
 template <int D, typename T, typename P, bool S, int PH>
 void launch_collide_vc(const lbm_solver *h, size_t m1) {
-    if constexpr (D == 3 && !S)
-        hipLaunchKernelGGL((lbm::k_collide_vc<T, P, PH>), dim3(8 * h->ztiles.per), dim3(lbm::ZCfg<T, P>::kThreads), 0,
-                           h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m1),
-                           ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
-                           ws_ptr<const T>(h, h->L.muF), grid_of(h), h->ztiles, phys_of<T>(h));
+    if constexpr (D == 3 && !S) {
+        if constexpr (lbm::PopFmt<P>::shifted) {
+            if (h->shift == LBM_SHIFT_WEIGHTS) {
+                launch_collide_vc_shift<T, P, PH, true>(h, m1);
+                return;
+            }
+        }
+        launch_collide_vc_shift<T, P, PH, false>(h, m1);
+    }
 }
 
 template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
