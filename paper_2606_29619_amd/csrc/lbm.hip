@@ -511,6 +511,13 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->analytic = p->grad_eps != nullptr;
     h->plane_step = plane_step_ok(p, nb) && workspace_bytes >= L.total;
     {
+        const CachedPasses c = cached_passes(step_bytes(N, Q, p->storage, p->scheme == LBM_SCHEME_LAGGED),
+                                             p->storage, whole_lines(p->nx, p->storage));
+        h->cached_mom = c.moments;
+        h->cached_col = c.collide;
+        h->cached_lag = c.lagged;
+    }
+    {
         // the fused correction-collision kernel: D3Q27, any storage, no solids, wet nodes,
         // Picard iterations or analytic derivatives, whole tiles; AUTO takes it where 256
         // workgroups leave each at least 16 planes (shorter chunks correct and stage too many

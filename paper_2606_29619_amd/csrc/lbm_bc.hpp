@@ -88,7 +88,7 @@ __device__ __forceinline__ P *read_slot(P *__restrict__ f, const uint8_t *__rest
     using L = Lat<D>;
     constexpr int cx = L::c[I][0], cy = L::c[I][1], cz = L::c[I][2];
     const uint32_t n = nb.self();
-    if constexpr (PH == 0 || (cx == 0 && cy == 0 && cz == 0)) {
+    if constexpr (!swapped(PH) || (cx == 0 && cy == 0 && cz == 0)) {
         return at(plane(f, I, g.N), n);
     } else {
         const uint32_t s = nb.at(-cx, -cy, -cz);

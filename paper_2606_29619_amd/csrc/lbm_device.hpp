@@ -139,6 +139,17 @@ __device__ __forceinline__ T ld(const T *base, uint32_t idx) {
 // those with c_x = 0 cover whole lines of one wave and stay non-temporal (256^3 box: FP32 step
 // 1.236 -> 1.218 ms, FP32 lagged pass 1.050 -> 1.026 ms; the moment pass with every load of the
 // swapped phase non-temporal was 0.6 % slower than with this rule).
+//
+// Template parameter PH of the passes: bit 0 the AA phase (0 natural, 1 swapped), bit 1 set where all
+// accesses go through the caches, which pays in two cases (cached_passes chooses):
+// a run whose populations, records and static fields stay in the 256 MB Infinity Cache from one pass
+// to the next (us per step, non-temporal and cached: FP32 box 70^3 46 -> 40, 100^3 97 -> 84, 115^3 153
+// -> 122, FP64 90^3 150 -> 124, FP32 lagged 100^3 77 -> 61; beyond, it costs: FP32 160^3 350 -> 380,
+// FP64 120^3 303 -> 335); and rows that are no whole 128-byte lines, whose ends waves share (FP16 220^3
+// collision 456 -> 387, lagged pass 671 -> 609, FP32 220^3 collision 609 -> 564, 150^3 208 -> 181; but
+// FP32 moment pass 271 -> 299, FP64 collision 145 -> 142 at 110^3 and 281 -> 286 at 140^3).
+constexpr bool swapped(int ph) { return (ph & 1) != 0; }
+constexpr bool cached(int ph) { return (ph & 2) != 0; }
 template <bool NT, typename T>
 __device__ __forceinline__ T ld_pop(const T *base, uint32_t idx) {
     if constexpr (NT) return __builtin_nontemporal_load(at(base, idx));
@@ -433,8 +444,8 @@ __device__ __forceinline__ P load_raw(const P *__restrict__ f, const uint8_t *__
     using L = Lat<D>;
     constexpr int cx = L::c[I][0], cy = L::c[I][1], cz = L::c[I][2];
     const uint32_t n = nb.self();
-    constexpr bool NT = PH == 0 || cx == 0;
-    if constexpr (PH == 0 || (cx == 0 && cy == 0 && cz == 0)) {
+    constexpr bool NT = !cached(PH) && (!swapped(PH) || cx == 0);
+    if constexpr (!swapped(PH) || (cx == 0 && cy == 0 && cz == 0)) {
         return ld_pop<NT>(plane(f, I, g.N), n);
     } else {
         const uint32_t s = nb.at(-cx, -cy, -cz);
@@ -481,9 +492,9 @@ __device__ __forceinline__ void store_pop(P *__restrict__ f, const uint8_t *__re
     using L = Lat<D>;
     constexpr int cx = L::c[I][0], cy = L::c[I][1], cz = L::c[I][2];
     const uint32_t n = nb.self();
-    constexpr bool NT = PH == 0 || cx == 0;
+    constexpr bool NT = !cached(PH) && (!swapped(PH) || cx == 0);
     const P raw = encode<D, I, P>(val, base * weight<D, I>());
-    if constexpr (PH == 0 || (cx == 0 && cy == 0 && cz == 0)) {
+    if constexpr (!swapped(PH) || (cx == 0 && cy == 0 && cz == 0)) {
         st_pop<NT>(plane(f, L::opp[I], g.N), n, raw);
     } else {
         const uint32_t d = nb.at(cx, cy, cz);
@@ -1287,7 +1298,7 @@ __device__ __forceinline__ void collide_populations(P *__restrict__ f,
     // (16-bit storage 0.76 -> 0.68 ms on the 256^3 box, FP64 2 % faster).  FP32 storage keeps
     // the addresses of the stencil loads: 7 instead of 4 waves per SIMD left its collision as
     // fast as before, and the recomputation cost 1 %.
-    constexpr bool kOpaque = PH == 1 && sizeof(P) != 4;
+    constexpr bool kOpaque = swapped(PH) && sizeof(P) != 4;
     const Nbr<D> nbp = kOpaque ? nb.opaque() : nb;
     auto collide_store = [&](auto gg) {
         constexpr int k = decltype(gg)::value;
@@ -1411,7 +1422,7 @@ __device__ __forceinline__ void fused_body_s(P *__restrict__ f, const P4<T> *__r
     corrected_velocity<D, T, SOLIDS>(m1p, ev, eps, mask, g, nb, own1, cs, own2.w);
     ProductForm<D, T> peq, pst;
     cell_equilibria<D, T, SOLIDS>(m2p, ev, eps, muD, muF, mask, g, ph, nb, own2, cs, peq, pst);
-    collide_stream<D, T, P, SOLIDS, PH>(f, mask, g, PH == 1 ? nb.opaque() : nb, fi, cs.vs.beta,
+    collide_stream<D, T, P, SOLIDS, PH>(f, mask, g, swapped(PH) ? nb.opaque() : nb, fi, cs.vs.beta,
                                         own_base<P>(ev.at(0, 0, 0), ph), peq, pst);
     store_rec<D>(m1n, n, own1.r, own1.w);
     store_rec<D>(m2n, n, own2.r, own2.w);
@@ -1613,8 +1624,8 @@ template <int D, typename T, typename P, bool SOLIDS, int PH, bool OCC = true>
 struct SolidAwareWaves {
     static constexpr bool on = SOLIDS && D == 3 && OCC;
     static constexpr bool half = sizeof(P) == 2, fp64 = sizeof(T) == 8;
-    static constexpr int collide = !on ? 1 : half ? (PH == 1 ? 5 : 6) : (fp64 && PH == 1 ? 3 : 1);
-    static constexpr int fused = on && half && PH == 0 ? 3 : 1;
+    static constexpr int collide = !on ? 1 : half ? (swapped(PH) ? 5 : 6) : (fp64 && swapped(PH) ? 3 : 1);
+    static constexpr int fused = on && half && !swapped(PH) ? 3 : 1;
 };
 
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD, bool OCC>

@@ -132,6 +132,7 @@ struct lbm_solver {
     bool fused_vc;      // velocity correction inside the collision pass (k_collide_vc)
     bool plane_step;    // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
     bool solid_occ;     // runs with solids: under a quarter of the tiles solid-aware
+    bool cached_mom, cached_col, cached_lag;  // cached population accesses (see lbm::cached)
     lbm::ZTiling ztiles;
     int device;         // HIP device current at creation
 };
@@ -270,6 +271,28 @@ struct RunTiles {
     lbm::Tiling moments;  // moment and lagged passes
 };
 RunTiles run_tiles(const lbm_params *p);
+
+// Which passes access the populations through the caches: all when the step's working set (bytes)
+// stays in the Infinity Cache, and on rows that are no whole cache lines the collision of FP32 and
+// 16-bit storage and the moment and lagged passes of 16-bit storage (both measured at lbm::cached; the
+// largest sets that gained held 231 MB, the smallest that lost 280 MB).
+constexpr int64_t kCachedSet = 240 << 20;
+struct CachedPasses {
+    bool moments, collide, lagged;
+};
+inline CachedPasses cached_passes(int64_t set, int storage, bool whole_lines) {
+    if (set <= kCachedSet) return {true, true, true};
+    const bool half = storage == LBM_F16_SHIFTED || storage == LBM_BF16_SHIFTED;
+    return {half && !whole_lines, storage != LBM_F64 && !whole_lines, half && !whole_lines};
+}
+// Bytes a step of the run works on: populations, static fields and records.
+inline int64_t step_bytes(int64_t N, int Q, int storage, bool lagged) {
+    const int s = storage == LBM_F64 ? 8 : 4, sp = storage == LBM_F64 ? 8 : (storage == LBM_F32 ? 4 : 2);
+    return N * (Q * sp + (3 + (lagged ? 16 : 8)) * s);
+}
+inline bool whole_lines(int nx, int storage) {
+    return (int64_t)nx * (storage == LBM_F64 ? 8 : (storage == LBM_F32 ? 4 : 2)) % 128 == 0;
+}
 
 // Workspace layout of a run with the shape and options of p (validates them; host only).
 int run_layout(const lbm_params *p, Layout *L);

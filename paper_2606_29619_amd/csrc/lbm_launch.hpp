@@ -16,13 +16,19 @@ namespace lbmh {
 // ---- kernel launchers, dispatched on (lattice, arithmetic type T, population storage type P,
 // solids, phase, derivative source) -------------------------------------------------------------
 template <int D, typename T, typename P, bool S, int PH, bool AD>
-void launch_moments(const lbm_solver *h, size_t m1_out) {
+void launch_moments_form(const lbm_solver *h, size_t m1_out) {
     auto ph = phys_of<T>(h);
     lbm::P4<T> *m0 = h->picard_iters ? ws_ptr<lbm::P4<T>>(h, h->L.m0) : nullptr;
     hipLaunchKernelGGL((lbm::k_moments<D, T, P, S, PH, AD>), tile_grid(h->mtiles), dim3(256), 0, h->stream,
                        ws_ptr<const P>(h, f_off(h)), ws_ptr<const T>(h, h->L.eps),
                        ws_ptr<const T>(h, h->L.muD), ws_ptr<const T>(h, h->L.muF), mask_ptr(h),
                        tsolid_ptr(h), ws_ptr<lbm::P4<T>>(h, m1_out), m0, grid_of(h), h->mtiles, ph);
+}
+
+template <int D, typename T, typename P, bool S, int PH, bool AD>
+void launch_moments(const lbm_solver *h, size_t m1_out) {
+    if (h->cached_mom) launch_moments_form<D, T, P, S, PH | 2, AD>(h, m1_out);
+    else launch_moments_form<D, T, P, S, PH, AD>(h, m1_out);
 }
 
 template <int D, typename T, bool S, bool AD>
@@ -58,7 +64,7 @@ void launch_collide_occ(const lbm_solver *h, size_t m2, size_t nbr) {
 // Runs with solids take the instantiation that requests the occupancy of the solid-free code
 // where few of their tiles are solid-aware (lbm_solver::solid_occ).
 template <int D, typename T, typename P, bool S, int PH, bool AD>
-void launch_collide(const lbm_solver *h, size_t m2, size_t nbr) {
+void launch_collide_form(const lbm_solver *h, size_t m2, size_t nbr) {
     if constexpr (S) {
         if (h->solid_occ) {
             launch_collide_occ<D, T, P, S, PH, AD, true>(h, m2, nbr);
@@ -66,6 +72,12 @@ void launch_collide(const lbm_solver *h, size_t m2, size_t nbr) {
         }
     }
     launch_collide_occ<D, T, P, S, PH, AD, false>(h, m2, nbr);
+}
+
+template <int D, typename T, typename P, bool S, int PH, bool AD>
+void launch_collide(const lbm_solver *h, size_t m2, size_t nbr) {
+    if (h->cached_col) launch_collide_form<D, T, P, S, PH | 2, AD>(h, m2, nbr);
+    else launch_collide_form<D, T, P, S, PH, AD>(h, m2, nbr);
 }
 
 template <typename T, typename P, int PH, bool WEIGHTS>
@@ -103,7 +115,7 @@ void launch_fused_occ(const lbm_solver *h, int prev, int next) {
 }
 
 template <int D, typename T, typename P, bool S, int PH, bool AD>
-void launch_fused(const lbm_solver *h, int prev, int next) {
+void launch_fused_form(const lbm_solver *h, int prev, int next) {
     if constexpr (S) {
         if (h->solid_occ) {
             launch_fused_occ<D, T, P, S, PH, AD, true>(h, prev, next);
@@ -111,6 +123,12 @@ void launch_fused(const lbm_solver *h, int prev, int next) {
         }
     }
     launch_fused_occ<D, T, P, S, PH, AD, false>(h, prev, next);
+}
+
+template <int D, typename T, typename P, bool S, int PH, bool AD>
+void launch_fused(const lbm_solver *h, int prev, int next) {
+    if (h->cached_lag) launch_fused_form<D, T, P, S, PH | 2, AD>(h, prev, next);
+    else launch_fused_form<D, T, P, S, PH, AD>(h, prev, next);
 }
 
 template <int D, typename T, typename P, bool S, bool AD>

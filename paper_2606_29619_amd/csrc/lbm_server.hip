@@ -213,6 +213,7 @@ struct Group {
     // device offsets in the pool; starts of the moment and lagged passes, and of the others
     size_t desc_off = 0, starts_off = 0, cstarts_off = 0;
     uint32_t nwg = 0, cnwg = 0;
+    CachedPasses cached{};  // population accesses of the group's passes
 };
 
 template <int D, typename T, typename P, bool S>
@@ -268,16 +269,20 @@ struct GroupOps {
         const uint32_t *starts = reinterpret_cast<const uint32_t *>(sv->pool + gr.starts_off);
         const uint32_t *cstarts = reinterpret_cast<const uint32_t *>(sv->pool + gr.cstarts_off);
         const int n = (int)gr.runs.size();
+        auto launch = [&](auto plain, auto cached, bool use_cached, uint32_t nwg, auto... args) {
+            hipLaunchKernelGGL((use_cached ? cached : plain), dim3(nwg), dim3(256), 0, sv->stream,
+                               runs, args...);
+        };
         if (gr.scheme == LBM_SCHEME_LAGGED) {
-            hipLaunchKernelGGL((lbm::kb_fused<D, T, P, S, PH>), dim3(gr.nwg), dim3(256), 0,
-                               sv->stream, runs, starts, n, parity);
+            launch(lbm::kb_fused<D, T, P, S, PH>, lbm::kb_fused<D, T, P, S, PH | 2>,
+                   gr.cached.lagged, gr.nwg, starts, n, parity);
         } else {
-            hipLaunchKernelGGL((lbm::kb_moments<D, T, P, S, PH>), dim3(gr.nwg), dim3(256), 0,
-                               sv->stream, runs, starts, n);
+            launch(lbm::kb_moments<D, T, P, S, PH>, lbm::kb_moments<D, T, P, S, PH | 2>,
+                   gr.cached.moments, gr.nwg, starts, n);
             hipLaunchKernelGGL((lbm::kb_vcorrect<D, T, P, S>), dim3(gr.cnwg), dim3(256), 0,
                                sv->stream, runs, cstarts, n);
-            hipLaunchKernelGGL((lbm::kb_collide<D, T, P, S, PH>), dim3(gr.cnwg), dim3(256), 0,
-                               sv->stream, runs, cstarts, n);
+            launch(lbm::kb_collide<D, T, P, S, PH>, lbm::kb_collide<D, T, P, S, PH | 2>,
+                   gr.cached.collide, gr.cnwg, cstarts, n);
         }
     }
 
@@ -533,6 +538,20 @@ LBM_API int lbm_server_progress(lbm_server *s, int64_t max_rounds, int64_t *fini
                 g = &groups.back();
             }
             g->runs.push_back(q);
+        }
+        // the runs of a round are stepped in turn, so their working sets share the caches
+        int64_t set = 0;
+        for (int64_t id : s->active) {
+            const lbm_solver *h = find_req(s, id)->h;
+            set += step_bytes(h->N, h->Q, h->storage, h->scheme == LBM_SCHEME_LAGGED);
+        }
+        for (auto &g : groups) {
+            int64_t ragged = 0, cells = 0;
+            for (const Request *q : g.runs) {
+                cells += q->h->N;
+                if (!whole_lines(q->h->nx, g.storage)) ragged += q->h->N;
+            }
+            g.cached = cached_passes(set, g.storage, 2 * ragged < cells);
         }
         s->table_host.clear();
         for (auto &g : groups) group_dispatch(g, FillOp{s, g, s->table_host});
