@@ -740,6 +740,16 @@ LBM_API int lbm_moments(lbm_solver *h, void *rho_dev, void *v_dev, int dtype, in
     if (dtype != LBM_DTYPE_F64 && dtype != LBM_DTYPE_F32) return fail(LBM_ERR_INVALID_ARG, "bad dtype");
     if (velocity_kind != LBM_VELOCITY_SUPERFICIAL && velocity_kind != LBM_VELOCITY_INTRINSIC)
         return fail(LBM_ERR_INVALID_ARG, "bad velocity_kind");
+    if (!h->bc_vp && !h->picard_iters) {
+        // nothing follows the velocity correction: it writes the caller's arrays
+        const bool lag = h->scheme == LBM_SCHEME_LAGGED && h->have_prev;
+        const int c = lag ? h->cur ^ 1 : h->cur;
+        if (h->bc_outflow) dispatch(h, BcOutflowPass{h});
+        dispatch(h, MomentsPass{h, h->L.m1[c]});
+        dispatch(h, MomentsOutPass{h, h->L.m1[c], h->L.m1[h->cur], rho_dev, v_dev, dtype, velocity_kind});
+        LAUNCH_CHECK();
+        return LBM_OK;
+    }
     const size_t m2 = current_moments(h);
     LAUNCH_CHECK();
     const int64_t N = h->N;

@@ -12,6 +12,7 @@ void dispatch_analytic(const lbm_solver *h, F &fn) {
 
 template void dispatch_analytic<MomentsPass>(const lbm_solver *, MomentsPass &);
 template void dispatch_analytic<VcorrectPass>(const lbm_solver *, VcorrectPass &);
+template void dispatch_analytic<MomentsOutPass>(const lbm_solver *, MomentsOutPass &);
 template void dispatch_analytic<CollidePass>(const lbm_solver *, CollidePass &);
 template void dispatch_analytic<PicardPass>(const lbm_solver *, PicardPass &);
 template void dispatch_analytic<FusedPass>(const lbm_solver *, FusedPass &);

@@ -41,13 +41,13 @@ void launch_picard(const lbm_solver *h, size_t vin, size_t vout) {
                        grid_of(h), h->tiles, ph, (T)h->picard_omega);
 }
 
-template <int D, typename T, bool S, bool AD>
-void launch_vcorrect(const lbm_solver *h, size_t own_src, size_t m1, size_t m2_out) {
+template <int D, typename T, bool S, bool AD, typename ST>
+void launch_vcorrect(const lbm_solver *h, size_t own_src, size_t m1, ST store) {
     auto ph = phys_of<T>(h);
-    hipLaunchKernelGGL((lbm::k_vcorrect<D, T, S, AD>), tile_grid(h->tiles), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL((lbm::k_vcorrect<D, T, S, AD, ST>), tile_grid(h->tiles), dim3(256), 0, h->stream,
                        ws_ptr<const lbm::P4<T>>(h, own_src), ws_ptr<const lbm::P4<T>>(h, m1),
                        ws_ptr<const T>(h, h->L.eps), mask_ptr(h), tsolid_ptr(h), tflat_ptr(h),
-                       ws_ptr<lbm::P4<T>>(h, m2_out), grid_of(h), h->tiles, ph);
+                       grid_of(h), h->tiles, ph, store);
 }
 
 template <int D, typename T, typename P, bool S, int PH, bool AD, bool OCC>
@@ -169,6 +169,9 @@ void launch_stats(const lbm_solver *h, size_t m2, double *part) {
 }
 
 // ---- wet-node boundary kernels (one thread per boundary node; boundaries imply solids) -----
+// The rebuild writes populations through the caches, as the collision reads them next (384 x 192 x 192
+// FP32 duct, rebuild and collision 950 -> 923 us; 150 x 100 x 100, where every pass does so, 111 -> 94);
+// the records' reads gain nothing from it (56 -> 75 us in the larger duct) and keep the hints.
 template <typename T>
 lbm::BNodes<T> bnodes_of(const lbm_solver *h) {
     return lbm::BNodes<T>{ws_ptr<const uint32_t>(h, h->L.bcell), ws_ptr<const uint32_t>(h, h->L.bcode),
@@ -226,7 +229,7 @@ struct BcRebuildPass {  // own records m2, stencil neighbours' nbr
     template <int D, typename T, typename P, bool S, int PH, bool AD>
     void operator()() {
         if constexpr (S)
-            hipLaunchKernelGGL((lbm::k_bc_rebuild<D, T, P, S, PH, AD>), bc_grid(h), dim3(lbm::kBcThreads), 0,
+            hipLaunchKernelGGL((lbm::k_bc_rebuild<D, T, P, S, PH | 2, AD>), bc_grid(h), dim3(lbm::kBcThreads), 0,
                                h->stream, ws_ptr<P>(h, f_off(h)), ws_ptr<const lbm::P4<T>>(h, m2),
                                ws_ptr<const lbm::P4<T>>(h, nbr),
                                ws_ptr<const T>(h, h->L.eps), ws_ptr<const T>(h, h->L.muD),
@@ -297,7 +300,29 @@ struct VcorrectPass {
     const lbm_solver *h;
     size_t own_src, m1, m2_out;
     template <int D, typename T, typename P, bool S, int PH, bool AD>
-    void operator()() { launch_vcorrect<D, T, S, AD>(h, own_src, m1, m2_out); }
+    void operator()() {
+        launch_vcorrect<D, T, S, AD>(h, own_src, m1,
+                                     lbm::StoreRec<D, T>{ws_ptr<lbm::P4<T>>(h, m2_out)});
+    }
+};
+struct MomentsOutPass {  // the velocity correction into the caller's arrays
+    static constexpr bool kDerivs = true;
+    const lbm_solver *h;
+    size_t own_src, m1;
+    void *rho, *v;
+    int dtype, kind;
+    template <int D, typename T, typename P, bool S, int PH, bool AD>
+    void operator()() {
+        if (dtype == LBM_DTYPE_F64) out<D, T, S, AD, double>();
+        else out<D, T, S, AD, float>();
+    }
+    template <int D, typename T, bool S, bool AD, typename O>
+    void out() {
+        launch_vcorrect<D, T, S, AD>(
+            h, own_src, m1,
+            lbm::StoreMoments<D, T, O>{static_cast<O *>(rho), static_cast<O *>(v),
+                                       ws_ptr<const T>(h, h->L.eps), (uint32_t)h->N, kind});
+    }
 };
 struct CollidePass {  // own records m2, stencil neighbours' nbr (= m2 in the two-pass scheme)
     static constexpr bool kDerivs = true;

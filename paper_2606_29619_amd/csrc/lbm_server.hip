@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void kb_vcorrect(const RunDesc<T, P> *__restri
                                                    const uint32_t *__restrict__ starts, int nrun) {
     const int r = find_run(starts, nrun, blockIdx.x);
     const RunDesc<T, P> &d = runs[r];
-    vcorrect_body<D, T, S, false>(d.m1[0], d.m1[0], d.eps, d.mask, d.m2[0], d.g, cells_of(d), d.ph,
-                           blockIdx.x - starts[r]);
+    vcorrect_body<D, T, S, false>(d.m1[0], d.m1[0], d.eps, d.mask, d.g, cells_of(d), d.ph,
+                                  blockIdx.x - starts[r], StoreRec<D, T>{d.m2[0]});
 }
 
 template <int D, typename T, typename P, bool S, int PH>
