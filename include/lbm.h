@@ -230,11 +230,12 @@ typedef struct lbm_params {
      * where the run allows it: D3Q27, no solid cells, no wet-node boundaries, no Picard
      * iterations, no analytic porosity derivatives, nx a multiple of 64 and ny of 8 (4 for FP64
      * storage); LBM_PASSES_AUTO does so where, in addition, the grid is
-     * large enough for z-chunks of at least 16 planes (about 2^21 cells).  D2Q9 runs of 256
-     * cells and more without wet-node boundaries, Picard iterations or analytic derivatives take the whole step in one
-     * launch under both, from one population buffer into a second.  Every other run, and
-     * LBM_PASSES_SEPARATE, uses the separate correction pass.  All give bitwise the same
-     * results. */
+     * large enough to give 256 workgroups 16 planes each (about 2^21 cells).  D2Q9 runs of 256
+     * cells and more without wet-node boundaries, Picard iterations or analytic derivatives
+     * take the whole step in one launch under both, from one population buffer into a second,
+     * unless the plane is so thin that the separate passes are the faster (see lbm_footprint).
+     * Every other run, and LBM_PASSES_SEPARATE, uses the separate correction pass.  All give
+     * bitwise the same results. */
     int passes;
 } lbm_params;
 

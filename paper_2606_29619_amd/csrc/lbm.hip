@@ -96,7 +96,7 @@ hipError_t one_step(lbm_solver *h, hipEvent_t *ev) {
         h->cur = nx;
     } else {
         const int c = h->cur;
-        if (h->plane_step) {
+        if (h->plane != kPlaneSeparate) {
             if (ev) e = hipEventRecord(ev[0], h->stream);
             if (ev && e == hipSuccess) e = hipEventRecord(ev[1], h->stream);
             launch_plane_step(h);
@@ -171,14 +171,46 @@ RunTiles run_tiles(const lbm_params *p) {
     return {make_tiling(nx, ny, nz, ragged && d3, tx), make_tiling(nx, ny, nz, false, 64)};
 }
 
-// Whole step in one launch (k_plane_step), from one population buffer into another: every
-// two-pass D2Q9 run of 256 cells and more without wet nodes, Picard iterations or analytic
-// derivatives.  A smaller grid has fewer cells than one workgroup has threads, its tile's rings wrap
-// onto the tile several times over, and it keeps the separate passes and their workspace size.
-bool plane_step_ok(const lbm_params *p, uint32_t nb) {
-    return p->lattice == LBM_D2Q9 && p->scheme == LBM_SCHEME_TWO_PASS && nb == 0 &&
-           (int64_t)p->nx * p->ny >= 256 &&
-           p->picard_iters == 0 && !p->grad_eps && p->passes != LBM_PASSES_SEPARATE;
+// Form of a D2Q9 step: separate passes, or the whole step in one launch (k_plane_step) of 8 x 8 or
+// 32 x 8 tiles.  One launch is possible for two-pass runs of 256 cells and more without wet nodes,
+// Picard iterations or analytic derivatives (a smaller grid has fewer cells than one workgroup has
+// threads) and taken where it is expected to be faster.  Each form's step is estimated from its
+// lanes, idle ones of tiles past the grid's edges included: least-squares fits to 71 shapes from
+// 1 x 1024 to 2000 x 2000 cells in each storage, periodic boxes and channels with walls.  The three
+// dependent launches of the separate passes cost some 10 us however small the run; the tiles of one
+// launch form the records of their rings too, which a plane much thinner than a tile does not repay.
+// us per step, separate and one launch: FP64 channel with walls 128 x 64 13.6 and 7.3, 8 x 65,536
+// 50 and 160; FP32 box 1019 x 977 44.5 and 26.5, 1 x 262,140 17 and 237; FP16 8 x 65,536 100 and 55
+// (its separate passes take rectangular tiles), 65,536 x 1 10.9 and 15.1.
+PlaneShape plane_shape(const lbm_params *p, uint32_t nb) {
+    if (p->lattice != LBM_D2Q9 || p->scheme != LBM_SCHEME_TWO_PASS || nb != 0 ||
+        (int64_t)p->nx * p->ny < 256 || p->picard_iters != 0 || p->grad_eps ||
+        p->passes == LBM_PASSES_SEPARATE)
+        return kPlaneSeparate;
+    struct Fit { double us, ns; };  // per step and per lane
+    static constexpr Fit fits[2][3][3] = {
+        // FP64, FP32, 16-bit: separate, 8 x 8, 32 x 8
+        {{{10.6, 0.0687}, {5.1, 0.0810}, {6.4, 0.0505}},
+         {{10.3, 0.0318}, {4.2, 0.0357}, {5.0, 0.0215}},
+         {{10.9, 0.0224}, {4.5, 0.0373}, {5.1, 0.0220}}},
+        {{{11.4, 0.0678}, {6.4, 0.1039}, {8.5, 0.0648}},  // with solids
+         {{10.4, 0.0307}, {5.5, 0.0460}, {6.4, 0.0266}},
+         {{11.6, 0.0235}, {6.1, 0.0463}, {6.8, 0.0278}}}};
+    const Fit *fit = fits[p->mask ? 1 : 0][p->storage == LBM_F64 ? 0 : (p->storage == LBM_F32 ? 1 : 2)];
+    const RunTiles t = run_tiles(p);
+    const int64_t separate = (tile_lanes(t.moments) + 2 * tile_lanes(t.cells)) / 3;
+    auto lanes = [&](int tx, int ty) {
+        return (int64_t)((p->nx + tx - 1) / tx) * tx * ((p->ny + ty - 1) / ty) * ty;
+    };
+    auto cost = [&](int form, int64_t n) { return fit[form].us + 1e-3 * fit[form].ns * (double)n; };
+    const double sep = cost(0, separate), small = cost(1, lanes(8, 8)), large = cost(2, lanes(32, 8));
+    // where the estimates are close the smaller tile is the safer choice, and one launch before
+    // separate passes but for FP64, whose separate passes the fit takes for slower than they are on
+    // small thin planes (4 x 16,384: 12.3 us, one launch 16.4)
+    const bool wide = large < 0.95 * small;
+    const double one = wide ? large : small;
+    if (sep < (p->storage == LBM_F64 ? one : 0.95 * one)) return kPlaneSeparate;
+    return wide ? kPlaneLarge : kPlaneSmall;
 }
 
 int validate_shape(const lbm_params *p, int *D, int *Q, size_t *sp, size_t *s, int64_t *N) {
@@ -369,7 +401,7 @@ int run_layout(const lbm_params *p, Layout *L) {
     const lbm::Tiling tl = run_tiles(p).cells;
     *L = make_layout(Q, D, (size_t)N, sp, s, p->mask != nullptr, p->scheme == LBM_SCHEME_LAGGED,
                      8 * (size_t)tl.per, nb, p->picard_iters > 0, p->grad_eps != nullptr,
-                     plane_step_ok(p, nb));
+                     plane_shape(p, nb) != kPlaneSeparate);
     return LBM_OK;
 }
 
@@ -465,7 +497,7 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     const lbm::Tiling &tiles = rt.cells;
     const Layout L = make_layout(Q, D, (size_t)N, sp, s, solids, p->scheme == LBM_SCHEME_LAGGED,
                                  8 * (size_t)tiles.per, nb, p->picard_iters > 0,
-                                 p->grad_eps != nullptr, plane_step_ok(p, nb));
+                                 p->grad_eps != nullptr, plane_shape(p, nb) != kPlaneSeparate);
     if (!dev_workspace) return fail(LBM_ERR_INVALID_ARG, "dev_workspace is NULL");
     if (reinterpret_cast<uintptr_t>(dev_workspace) % 256)
         return fail(LBM_ERR_WORKSPACE, "dev_workspace must be 256-byte aligned");
@@ -509,7 +541,7 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->picard_iters = p->picard_iters;
     h->picard_omega = p->picard_omega;
     h->analytic = p->grad_eps != nullptr;
-    h->plane_step = plane_step_ok(p, nb) && workspace_bytes >= L.total;
+    h->plane = workspace_bytes >= L.total ? plane_shape(p, nb) : kPlaneSeparate;
     {
         const CachedPasses c = cached_passes(step_bytes(N, Q, p->storage, p->scheme == LBM_SCHEME_LAGGED),
                                              p->storage, whole_lines(p->nx, p->storage));
@@ -720,7 +752,7 @@ LBM_API int lbm_step_timed(lbm_solver *h, int64_t n, double kernel_ms[3]) {
                 // a two-pass step with the correction inside the collision pass has no
                 // correction kernel, one in a single launch only the collision's: the shares of
                 // the others are 0 and the collision's interval spans them
-                const int first = h->plane_step ? 0 : (h->fused_vc ? 1 : 2);
+                const int first = h->plane != kPlaneSeparate ? 0 : (h->fused_vc ? 1 : 2);
                 if (j >= first && j < 2) continue;
                 const int j0 = j == 2 ? first : j;
                 float ms = 0.f;

@@ -102,6 +102,9 @@ inline Layout make_layout(int Q, int D, size_t N, size_t sp, size_t s, bool soli
 
 inline bool is_finite(double x) { return std::isfinite(x); }
 
+// Form of a two-pass D2Q9 step: separate passes, or one launch of 8 x 8 or 32 x 8 tiles.
+enum PlaneShape { kPlaneSeparate, kPlaneSmall, kPlaneLarge };
+
 }  // namespace lbmh
 
 struct lbm_solver {
@@ -130,7 +133,7 @@ struct lbm_solver {
     lbm::Tiling tiles;  // 256-cell tiles, blocked, in XCD-contiguous ranges: collision and others
     lbm::Tiling mtiles; // the same of the moment and lagged passes (see run_tiles)
     bool fused_vc;      // velocity correction inside the collision pass (k_collide_vc)
-    bool plane_step;    // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
+    lbmh::PlaneShape plane;  // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
     bool solid_occ;     // runs with solids: under a quarter of the tiles solid-aware
     bool cached_mom, cached_col, cached_lag;  // cached population accesses (see lbm::cached)
     lbm::ZTiling ztiles;
@@ -241,6 +244,9 @@ inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
     return t;
 }
 
+// Lanes of a pass over one plane, those past the grid's edges included.
+inline int64_t tile_lanes(const lbm::Tiling &t) { return (int64_t)256 * t.ntx * t.nty; }
+
 // Grid of a cell pass: workgroups of one tile, padded to the same number on each XCD.
 inline dim3 tile_grid(const lbm::Tiling &t) { return dim3((unsigned)(8 * (int64_t)t.per)); }
 
@@ -250,7 +256,9 @@ T *ws_ptr(const lbm_solver *h, size_t off) {
 }
 
 // Offset of the population buffer that holds the current state.
-inline size_t f_off(const lbm_solver *h) { return h->plane_step && h->phase ? h->L.f2 : h->L.f; }
+inline size_t f_off(const lbm_solver *h) {
+    return h->plane != kPlaneSeparate && h->phase ? h->L.f2 : h->L.f;
+}
 
 inline const uint8_t *mask_ptr(const lbm_solver *h) {
     return h->solids ? reinterpret_cast<const uint8_t *>(h->ws + h->L.mask) : nullptr;
@@ -297,7 +305,7 @@ inline bool whole_lines(int nx, int storage) {
 // Workspace layout of a run with the shape and options of p (validates them; host only).
 int run_layout(const lbm_params *p, Layout *L);
 
-// Enqueue one D2Q9 step of a run with plane_step (lbm_plane.hip).
+// Enqueue one D2Q9 step of a run stepped in one launch (lbm_plane.hip).
 void launch_plane_step(const lbm_solver *h);
 
 // Enqueue the statistics of the current state into res (8 doubles, the lbm_stats slots) with the
