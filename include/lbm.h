@@ -218,12 +218,13 @@ typedef struct lbm_params {
      * that is not finite on a fluid cell: LBM_ERR_INVALID_ARG. */
     const double *grad_eps;
     const double *hess_eps;
-    /* Workgroup tiles of the cell passes: LBM_TILES_AUTO picks rows of 256, 128 or 64 cells and,
-     * for an x extent that is not a multiple of 64 (16-bit storage: D3Q27 runs whose rows would
-     * leave at least 30 % of the lanes idle), packed rows (256
-     * consecutive cells of a plane, wrapping from row to row); LBM_TILES_RECTANGULAR never
-     * packs.  The tiles decide only which thread updates which cell: results are bitwise the
-     * same. */
+    /* Workgroup tiles of the cell passes: LBM_TILES_AUTO picks rows of 256, 128 or 64 cells or
+     * packed rows (256 consecutive cells of a plane, wrapping from row to row).  FP32 and FP64
+     * storage: packed for an x extent that is not a multiple of 64.  16-bit storage: never on
+     * D2Q9; on D3Q27 packed for such an extent in the collision, and in the moment and lagged
+     * passes for rows much narrower than a tile; with solids one kind for all passes, packed where such rows would
+     * leave at least 30 % of the lanes idle.  LBM_TILES_RECTANGULAR never packs.  The tiles
+     * decide only which thread updates which cell: results are bitwise the same. */
     int tiles;
     /* Kernels of a two-pass step.  LBM_PASSES_FUSED corrects the velocity inside the
      * collision pass (two kernels per step, the corrected velocities shared through LDS)

@@ -147,16 +147,12 @@ int check_handle(const lbm_solver *h) {
 
 // Tiles of a run.  FP32 and FP64 storage: packed rows for x extents that are not a multiple of 64,
 // in every pass, unless the caller asks for rectangular tiles.
-// 16-bit storage: the moment and lagged passes read the porosity of their decode (the 26 neighbours of
-// a D3Q27 cell) from LDS, staged for a rectangular tile, and take the narrowest tile, whose halo is the
-// smallest (64 x 4: 1,188 values, 256 x 1: 2,322; 256 x 192 x 192 FP16 moment pass 161 against 184 us,
-// 192^3 BF16 lagged pass 376 against 455 us); the collision stages nothing and, on D3Q27, takes packed
-// rows like FP32's.  FP16 150^3, moment and collision pass: packed 123 + 145 us, rectangular 64 x 4
-// 76 + 180 us; 200^3 275 + 306 and 158 + 469 us.  With solids the passes share one set of tile flags
-// and so one kind of tile: packed where a D3Q27 run's rectangular tiles would leave at least 30 % of
-// the lanes idle.
+// 16-bit storage: the collision, which stages nothing, takes packed rows like FP32's on D3Q27 (FP16
+// 150^3 145 us packed, 180 rectangular; 200^3 306 and 469) and rectangular tiles on D2Q9; the moment and lagged passes choose for themselves (moment_tiles).  With solids the passes share one
+// set of tile flags and so one kind of tile: packed where a D3Q27 run's rectangular tiles would leave
+// at least 30 % of the lanes idle.
 RunTiles run_tiles(const lbm_params *p) {
-    const int nx = p->nx, ny = p->ny, nz = p->nz, tx = rect_tile_x(nx);
+    const int nx = p->nx, ny = p->ny, nz = p->nz, tx = rect_tile_x(nx, ny);
     const bool ragged = nx % 64 != 0 && p->tiles != LBM_TILES_RECTANGULAR;
     if (p->storage == LBM_F32 || p->storage == LBM_F64) {
         const lbm::Tiling t = make_tiling(nx, ny, nz, ragged, tx);
@@ -168,7 +164,8 @@ RunTiles run_tiles(const lbm_params *p) {
         const lbm::Tiling t = make_tiling(nx, ny, nz, ragged && d3 && 10 * (padded - nx) >= 3 * padded, tx);
         return {t, t};
     }
-    return {make_tiling(nx, ny, nz, ragged && d3, tx), make_tiling(nx, ny, nz, false, 64)};
+    return {make_tiling(nx, ny, nz, ragged && d3, tx),
+            moment_tiles(nx, ny, nz, d3, ragged && d3, p->scheme == LBM_SCHEME_LAGGED)};
 }
 
 // Form of a D2Q9 step: separate passes, or the whole step in one launch (k_plane_step) of 8 x 8 or

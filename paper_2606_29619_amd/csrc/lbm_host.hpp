@@ -212,23 +212,32 @@ inline lbm::ZTiling make_ztiling(int nx, int ny, int nz, int tx, int ty) {
     return z;
 }
 
-// Width of the rectangular row tiles (256 x 1, 128 x 2 or 64 x 4 cells) for an x extent nx: the one
-// that leaves the fewest lanes past the row's end, a wider tile being worth 3 % of padding per
-// doubling (fewer tile edges in x).  us per step of the separate FP32 passes at widths 64 / 128 /
-// 256: 320 x 192 x 150 823 / 828 / 1,023; 384 x 192 x 192 1,280 / 1,251 / 1,443; 448 x 160 x 100
-// 617 / 659 / 650; 256 x 192 x 192 869 / 857 / 827; FP64 192^3 1,319 / 1,507 / 1,340.
-inline int rect_tile_x(int nx) {
-    int best = 256;
-    int64_t cost = INT64_MAX;
-    for (int tx = 256, pct = 100; tx >= 64; tx /= 2, pct += 3) {
-        const int64_t c = (int64_t)((nx + tx - 1) / tx) * tx * pct;
-        if (c < cost) {
+// Width of the rectangular row tiles (256 x 1, 128 x 2 or 64 x 4 cells) of an nx x ny plane: the one
+// with the fewest lanes past the grid's edges, times `factor` for each doubling of the width.  Lanes
+// past a row's end idle in a working wave; a row past the plane's edge is a wave that ends early and
+// counts `edge` of one.
+inline int tile_x(int nx, int ny, double factor, double edge, double *lanes = nullptr) {
+    int best = 0;
+    double cost = 0.0, f = 1.0;
+    for (int tx = 64; tx <= 256; tx *= 2, f *= factor) {
+        const int ty = 256 / tx;
+        const double rows = (1 - edge) * ny + edge * ((ny + ty - 1) / ty * ty);
+        const double c = f * ((nx + tx - 1) / tx * tx) * rows;
+        if (best == 0 || c < cost) {
             cost = c;
             best = tx;
         }
     }
+    if (lanes) *lanes = cost;
     return best;
 }
+
+// Width for the passes that stage nothing: a wider tile is worth 3 % of idle lanes per doubling (fewer
+// tile edges in x).  us per step of the separate FP32 passes at widths 64 / 128 / 256: 320 x 192 x 150
+// 823 / 828 / 1,023; 384 x 192 x 192 1,280 / 1,251 / 1,443; 448 x 160 x 100 617 / 659 / 650;
+// 256 x 192 x 192 869 / 857 / 827; FP64 192^3 1,319 / 1,507 / 1,340.  Few rows, 64 and 256 wide: FP32
+// 192 x 1 x 4096 66 / 58, 448 x 3 x 2048 215 / 224, FP64 473 / 495.
+inline int rect_tile_x(int nx, int ny) { return tile_x(nx, ny, 0.97, 0.12); }
 
 // Tiles of the cell passes: rectangular tiles of tx cells along x, or packed rows, so that rows of,
 // say, 70 cells do not leave most of a second wave idle.
@@ -242,6 +251,25 @@ inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
     t.nty = (ny + t.ty - 1) / t.ty;
     lbm::block_tiles(t, nz);
     return t;
+}
+
+// Tiles of the 16-bit moment and lagged passes without solids.
+// Rectangular tiles stage the porosity of the decode (the 26 neighbours of a D3Q27 cell) in LDS.  The
+// narrowest has the smallest halo (64 x 4: 1,188 values, 256 x 1: 2,322), which the moment pass feels
+// (256 x 192 x 192 FP16, widths 64 / 128 / 256: 161 / 173 / 184 us) and the lagged pass hardly (224^3
+// BF16 675 / 672 / 687 us) except on D2Q9, where it has less else to do (65,536 x 3: 7.4 and 9.4 us);
+// but three of its four rows lie past the edge of a plane of one row, and each stages all the same
+// (256 x 1 x 4096 FP16, 64 and 256 wide: moments 44 and 26 us, lagged 86 and 52; 512 x 3 x 2048 lagged
+// 171 and 160).
+// Packed rows (can_pack: a ragged D3Q27 run) read that porosity through the caches, at some three
+// times the moment pass's time per lane and over twice the lagged pass's
+// (packed and rectangular, 192 x 160 rows of 9 cells: moments 13 and 31 us, lagged 25 and 77; of 25:
+// 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).
+inline lbm::Tiling moment_tiles(int nx, int ny, int nz, bool d3, bool can_pack, bool lagged) {
+    double lanes;
+    const int tx = tile_x(nx, ny, lagged && d3 ? 1.01 : 1.07, 0.25, &lanes);
+    const double packed = (lagged ? 2.35 : 3.0) * nx * ny;
+    return make_tiling(nx, ny, nz, can_pack && packed < lanes, tx);
 }
 
 // Lanes of a pass over one plane, those past the grid's edges included.
