@@ -222,7 +222,8 @@ typedef struct lbm_params {
      * packed rows (256 consecutive cells of a plane, wrapping from row to row).  FP32 and FP64
      * storage: packed for an x extent that is not a multiple of 64.  16-bit storage: never on
      * D2Q9; on D3Q27 packed for such an extent in the collision, and in the moment and lagged
-     * passes for rows much narrower than a tile; with solids one kind for all passes, packed where such rows would
+     * passes for rows much narrower than a tile (under the lattice-weight shift: where a fifth of
+     * the lanes would idle); with solids one kind for all passes, packed where such rows would
      * leave at least 30 % of the lanes idle.  LBM_TILES_RECTANGULAR never packs.  The tiles
      * decide only which thread updates which cell: results are bitwise the same. */
     int tiles;

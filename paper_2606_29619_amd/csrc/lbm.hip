@@ -165,7 +165,8 @@ RunTiles run_tiles(const lbm_params *p) {
         return {t, t};
     }
     return {make_tiling(nx, ny, nz, ragged && d3, tx),
-            moment_tiles(nx, ny, nz, d3, ragged && d3, p->scheme == LBM_SCHEME_LAGGED)};
+            moment_tiles(nx, ny, nz, d3, ragged && d3, p->scheme == LBM_SCHEME_LAGGED,
+                         p->shift == LBM_SHIFT_WEIGHTS)};
 }
 
 // Form of a D2Q9 step: separate passes, or the whole step in one launch (k_plane_step) of 8 x 8 or
@@ -539,13 +540,7 @@ LBM_API int lbm_create(const lbm_params *p, void *dev_workspace, size_t workspac
     h->picard_omega = p->picard_omega;
     h->analytic = p->grad_eps != nullptr;
     h->plane = workspace_bytes >= L.total ? plane_shape(p, nb) : kPlaneSeparate;
-    {
-        const CachedPasses c = cached_passes(step_bytes(N, Q, p->storage, p->scheme == LBM_SCHEME_LAGGED),
-                                             p->storage, whole_lines(p->nx, p->storage));
-        h->cached_mom = c.moments;
-        h->cached_col = c.collide;
-        h->cached_lag = c.lagged;
-    }
+    set_cached(h, cached_passes(step_bytes(h), h->storage, ragged_lines(h), staged_ragged(h)));
     {
         // the fused correction-collision kernel: D3Q27, any storage, no solids, wet nodes,
         // Picard iterations or analytic derivatives, whole tiles; AUTO takes it where 256

@@ -458,7 +458,11 @@ __device__ __forceinline__ P load_raw(const P *__restrict__ f, const uint8_t *__
 }
 
 // Shift of the f_I found at cell n (0 for FP64/FP32 storage): the porosity of its source cell,
-// the upstream neighbour n - c_I or n itself after a bounce-back.
+// the upstream neighbour n - c_I or n itself after a bounce-back.  Both shift rules
+// take one form (shift_base): a branch around the porosity read, which the lattice-weight shift does not
+// need, costs more than it spares in the collision (FP16 duct 384 x 192 x 192 without and with it:
+// porous shift 762 and 1,087 us, weights 762 and 837; 200^3 274 and 300, 274 and 265) and where the
+// porosity lies in LDS (256^3 moment pass 275 and 293).  load_pop's EARLY is for the rest.
 template <int D, bool SOLIDS, int I, typename P, typename T, typename E>
 __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, const E &ev,
                                             const Phys<T> &ph, const Nbr<D> &nb) {
@@ -476,11 +480,15 @@ __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, co
     }
 }
 
-template <int D, bool SOLIDS, int PH, int I, typename T, typename P, typename E>
+// EARLY: a uniform branch spares the lattice-weight shift the read of the source cell's porosity.
+template <int D, bool SOLIDS, int PH, int I, bool EARLY = false, typename T, typename P, typename E>
 __device__ __forceinline__ T load_pop(const P *__restrict__ f, const uint8_t *__restrict__ mask,
                                       const E &ev, const Phys<T> &ph, const Grid &g,
                                       const Nbr<D> &nb) {
     const P raw = load_raw<D, SOLIDS, PH, I>(f, mask, g, nb);
+    if constexpr (EARLY && PopFmt<P>::shifted) {
+        if (ph.shift_a == 0.0f) return decode<D, I, T>(raw, ph.shift_b * weight<D, I>());
+    }
     return decode<D, I, T>(raw, load_sigma<D, SOLIDS, I, P>(mask, ev, ph, nb));
 }
 
@@ -1223,7 +1231,7 @@ __device__ __forceinline__ void moments_body_s(const P *__restrict__ f,
     T fi[L::Q];
     unroll<0, L::Q>([&](auto ii) {
         constexpr int i = decltype(ii)::value;
-        fi[i] = load_pop<D, SOLIDS, PH, i>(f, mask, ev, ph, g, nb);
+        fi[i] = load_pop<D, SOLIDS, PH, i, !STAGE && !SOLIDS>(f, mask, ev, ph, g, nb);
     });
     T v0[3];
     const Rec<T> q = cell_moments<D, AD>(fi, ev, muD, muF, nb, ph, m0_out ? v0 : nullptr);
@@ -1441,7 +1449,7 @@ __device__ __forceinline__ void fused_body_s(P *__restrict__ f, const P4<T> *__r
     T fi[L::Q];
     unroll<0, L::Q>([&](auto ii) {
         constexpr int i = decltype(ii)::value;
-        fi[i] = load_pop<D, SOLIDS, PH, i>(f, mask, ev, ph, g, nb);
+        fi[i] = load_pop<D, SOLIDS, PH, i, !STAGE && !SOLIDS>(f, mask, ev, ph, g, nb);
     });
     const Rec<T> own1 = cell_moments<D, AD>(fi, ev, muD, muF, nb, ph);
     const CellStatic<D, T> cs = cell_static<D, AD>(ev, ph, n, own1.e);
@@ -1516,15 +1524,17 @@ __global__ __launch_bounds__(256) void k_picard(const P4<T> *__restrict__ vin,
 }
 
 // The moment and lagged passes of a tile: 16-bit storage stages the porosity its decode reads
-// in LDS on rectangular tiles and reads it through the caches on packed rows (ragged x extents),
-// whose tiles have no rectangular halo.  Same values either way.
+// in LDS on rectangular tiles and reads it through the caches on packed rows (ragged x extents of
+// D3Q27 runs), whose tiles have no rectangular halo; there the lattice-weight shift, which needs no
+// porosity to decode, leaves early (FP16 66 x 192 x 160 without and with it: moment pass 52 and 28 us,
+// lagged pass 140 and 77).  Same values either way.
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
 __device__ __forceinline__ void moments_body(const P *__restrict__ f, const T *__restrict__ eps,
                                              const T *__restrict__ muD, const T *__restrict__ muF,
                                              const uint8_t *__restrict__ mask,
                                              P4<T> *__restrict__ m1_out, P4<T> *__restrict__ m0_out,
                                              Grid g, Tiling tl, Phys<T> ph, uint32_t wg) {
-    if constexpr (PopFmt<P>::shifted) {
+    if constexpr (PopFmt<P>::shifted && D == 3) {
         if (tl.packed) {
             moments_body_s<D, T, P, SOLIDS, PH, AD, false>(f, eps, muD, muF, mask, m1_out, m0_out,
                                                            g, tl, ph, wg);
@@ -1542,7 +1552,7 @@ __device__ __forceinline__ void fused_body(P *__restrict__ f, const P4<T> *__res
                                            const T *__restrict__ muD, const T *__restrict__ muF,
                                            const uint8_t *__restrict__ mask, Grid g, Tiling tl,
                                            Phys<T> ph, uint32_t wg) {
-    if constexpr (PopFmt<P>::shifted) {
+    if constexpr (PopFmt<P>::shifted && D == 3) {
         if (tl.packed) {
             fused_body_s<D, T, P, SOLIDS, PH, AD, false>(f, m1p, m2p, m1n, m2n, eps, muD, muF,
                                                          mask, g, tl, ph, wg);

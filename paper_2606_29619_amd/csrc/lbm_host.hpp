@@ -262,13 +262,16 @@ inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
 // (256 x 1 x 4096 FP16, 64 and 256 wide: moments 44 and 26 us, lagged 86 and 52; 512 x 3 x 2048 lagged
 // 171 and 160).
 // Packed rows (can_pack: a ragged D3Q27 run) read that porosity through the caches, at some three
-// times the moment pass's time per lane and over twice the lagged pass's
+// times the moment pass's time per lane under the porous shift and over twice the lagged pass's
 // (packed and rectangular, 192 x 160 rows of 9 cells: moments 13 and 31 us, lagged 25 and 77; of 25:
-// 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).
-inline lbm::Tiling moment_tiles(int nx, int ny, int nz, bool d3, bool can_pack, bool lagged) {
+// 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).  The
+// lattice-weight shift needs none of it, and packing pays from a fifth of idle lanes (192 x 160 rows
+// of 66: moments 28 and 52 us, of 17: 11 and 30; 150^3 lagged 173 and 206).
+inline lbm::Tiling moment_tiles(int nx, int ny, int nz, bool d3, bool can_pack, bool lagged,
+                                bool weights) {
     double lanes;
     const int tx = tile_x(nx, ny, lagged && d3 ? 1.01 : 1.07, 0.25, &lanes);
-    const double packed = (lagged ? 2.35 : 3.0) * nx * ny;
+    const double packed = (weights ? 1.2 : (lagged ? 2.35 : 3.0)) * nx * ny;
     return make_tiling(nx, ny, nz, can_pack && packed < lanes, tx);
 }
 
@@ -310,25 +313,36 @@ RunTiles run_tiles(const lbm_params *p);
 
 // Which passes access the populations through the caches: all when the step's working set (bytes)
 // stays in the Infinity Cache, and on rows that are no whole cache lines the collision of FP32 and
-// 16-bit storage and the moment and lagged passes of 16-bit storage (both measured at lbm::cached; the
-// largest sets that gained held 231 MB, the smallest that lost 280 MB).
+// 16-bit storage and the 16-bit moment and lagged passes on staged tiles (measured at lbm::cached; the
+// largest sets that gained held 231 MB, the smallest that lost 280 MB).  On packed rows those two lose
+// like FP32's moment pass (FP16, lattice-weight shift, non-temporal and cached: 200^3 moments 120 and
+// 135 us, 81 x 256 x 256 74 and 91; 81 x 192 x 160 lagged pass 111 and 121).
 constexpr int64_t kCachedSet = 240 << 20;
 struct CachedPasses {
     bool moments, collide, lagged;
 };
-inline CachedPasses cached_passes(int64_t set, int storage, bool whole_lines) {
+inline CachedPasses cached_passes(int64_t set, int storage, bool ragged, bool staged_ragged) {
     if (set <= kCachedSet) return {true, true, true};
     const bool half = storage == LBM_F16_SHIFTED || storage == LBM_BF16_SHIFTED;
-    return {half && !whole_lines, storage != LBM_F64 && !whole_lines, half && !whole_lines};
+    return {half && staged_ragged, storage != LBM_F64 && ragged, half && staged_ragged};
+}
+inline void set_cached(lbm_solver *h, const CachedPasses &c) {
+    h->cached_mom = c.moments;
+    h->cached_col = c.collide;
+    h->cached_lag = c.lagged;
 }
 // Bytes a step of the run works on: populations, static fields and records.
-inline int64_t step_bytes(int64_t N, int Q, int storage, bool lagged) {
-    const int s = storage == LBM_F64 ? 8 : 4, sp = storage == LBM_F64 ? 8 : (storage == LBM_F32 ? 4 : 2);
-    return N * (Q * sp + (3 + (lagged ? 16 : 8)) * s);
+inline int64_t step_bytes(const lbm_solver *h) {
+    const int s = h->storage == LBM_F64 ? 8 : 4;
+    const int sp = h->storage == LBM_F64 ? 8 : (h->storage == LBM_F32 ? 4 : 2);
+    return h->N * (h->Q * sp + (3 + (h->scheme == LBM_SCHEME_LAGGED ? 16 : 8)) * s);
 }
-inline bool whole_lines(int nx, int storage) {
-    return (int64_t)nx * (storage == LBM_F64 ? 8 : (storage == LBM_F32 ? 4 : 2)) % 128 == 0;
+// Rows of populations that are no whole cache lines, and such rows under rectangular moment tiles.
+inline bool ragged_lines(const lbm_solver *h) {
+    const int sp = h->storage == LBM_F64 ? 8 : (h->storage == LBM_F32 ? 4 : 2);
+    return (int64_t)h->nx * sp % 128 != 0;
 }
+inline bool staged_ragged(const lbm_solver *h) { return ragged_lines(h) && !h->mtiles.packed; }
 
 // Workspace layout of a run with the shape and options of p (validates them; host only).
 int run_layout(const lbm_params *p, Layout *L);

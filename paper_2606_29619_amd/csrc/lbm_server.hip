@@ -541,17 +541,15 @@ LBM_API int lbm_server_progress(lbm_server *s, int64_t max_rounds, int64_t *fini
         }
         // the runs of a round are stepped in turn, so their working sets share the caches
         int64_t set = 0;
-        for (int64_t id : s->active) {
-            const lbm_solver *h = find_req(s, id)->h;
-            set += step_bytes(h->N, h->Q, h->storage, h->scheme == LBM_SCHEME_LAGGED);
-        }
+        for (int64_t id : s->active) set += step_bytes(find_req(s, id)->h);
         for (auto &g : groups) {
-            int64_t ragged = 0, cells = 0;
+            int64_t ragged = 0, staged = 0, cells = 0;
             for (const Request *q : g.runs) {
                 cells += q->h->N;
-                if (!whole_lines(q->h->nx, g.storage)) ragged += q->h->N;
+                if (ragged_lines(q->h)) ragged += q->h->N;
+                if (staged_ragged(q->h)) staged += q->h->N;
             }
-            g.cached = cached_passes(set, g.storage, 2 * ragged < cells);
+            g.cached = cached_passes(set, g.storage, 2 * ragged >= cells, 2 * staged >= cells);
         }
         s->table_host.clear();
         for (auto &g : groups) group_dispatch(g, FillOp{s, g, s->table_host});

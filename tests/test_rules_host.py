@@ -70,8 +70,8 @@ def test_runs_without_a_second_buffer():
 WRAPPER = r"""
 #include "lbm_host.hpp"
 // width (0: packed rows) and workgroups of the 16-bit moment tiles; width of the other tiles
-extern "C" void moment_tiles(int nx, int ny, int nz, int pack, int lagged, int64_t out[2]) {
-    const lbm::Tiling t = lbmh::moment_tiles(nx, ny, nz, true, pack, lagged);
+extern "C" void moment_tiles(int nx, int ny, int nz, int pack, int lagged, int weights, int64_t out[2]) {
+    const lbm::Tiling t = lbmh::moment_tiles(nx, ny, nz, true, pack, lagged, weights);
     out[0] = t.packed ? 0 : t.tx;
     out[1] = 8 * (int64_t)t.per;
 }
@@ -92,10 +92,10 @@ def tiles(tmp_path_factory):
                     "-o", str(d / "rules.so"), str(d / "rules.hip")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
 
-    def moment(nx, ny, nz, lagged=False, pack=None):
+    def moment(nx, ny, nz, lagged=False, weights=False, pack=None):
         out = (ctypes.c_int64 * 2)()
         lib.moment_tiles(nx, ny, nz, int(nx % 64 != 0 if pack is None else pack), int(lagged),
-                         out)
+                         int(weights), out)
         return out[0], out[1]
 
     return moment, lib.rect_tile_x
@@ -112,6 +112,16 @@ def test_moment_tiles_of_narrow_rows(tiles, lagged):
         assert nx * ny * nz < 2 ** 28 and 256 * moment(nx, ny, nz, lagged)[1] < 2 ** 32
     for nx in (37, 50, 70, 107, 150, 200, 220):
         assert moment(nx, 192, 160, lagged)[0] == 64, nx
+
+
+@pytest.mark.parametrize("lagged", [False, True])
+def test_moment_tiles_under_the_weight_shift(tiles, lagged):
+    """No porosity in the decode: packed like FP32's where a fifth of the lanes would idle."""
+    moment, _ = tiles
+    for nx in (17, 33, 50, 66, 70, 100, 150):
+        assert moment(nx, 192, 160, lagged, weights=True)[0] == 0, nx
+    for nx in (60, 107, 120, 220, 250):
+        assert moment(nx, 192, 160, lagged, weights=True)[0] == 64, nx
 
 
 def test_tiles_of_planes_of_few_rows(tiles):
