@@ -539,7 +539,8 @@ LBM_API int lbm_server_progress(lbm_server *s, int64_t max_rounds, int64_t *fini
             }
             g->runs.push_back(q);
         }
-        // the runs of a round are stepped in turn, so their working sets share the caches
+        // the runs of a round, those on launches of their own too, are stepped in turn, so their
+        // working sets share the caches
         int64_t set = 0;
         for (int64_t id : s->active) set += step_bytes(find_req(s, id)->h);
         for (auto &g : groups) {
@@ -551,6 +552,8 @@ LBM_API int lbm_server_progress(lbm_server *s, int64_t max_rounds, int64_t *fini
             }
             g.cached = cached_passes(set, g.storage, 2 * ragged >= cells, 2 * staged >= cells);
         }
+        for (Request *q : solo)
+            set_cached(q->h, cached_passes(set, q->h->storage, ragged_lines(q->h), staged_ragged(q->h)));
         s->table_host.clear();
         for (auto &g : groups) group_dispatch(g, FillOp{s, g, s->table_host});
         HIP_TRY(hipMemcpyAsync(s->pool + s->table_off, s->table_host.data(), s->table_host.size(),
