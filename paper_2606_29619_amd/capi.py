@@ -363,6 +363,15 @@ def make_params(lattice: int, storage: int, eps: np.ndarray, kappa: np.ndarray,
     return p, keep
 
 
+def _separate_footprint(params: lbm_params) -> int:
+    """Workspace of the run in separate passes, the least that lbm_create takes."""
+    passes, params.passes = params.passes, LBM_PASSES_SEPARATE
+    try:
+        return lbm_footprint(params)
+    finally:
+        params.passes = passes
+
+
 class Solver:
     """A solver on one GPU: owns its torch workspace, uses torch's current stream."""
 
@@ -380,7 +389,16 @@ class Solver:
         self.device = torch.device(device)
         self._owned = handle is None
         if handle is None:
-            self.workspace = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
+            try:
+                self.workspace = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                # a run stepped in one launch also steps, in separate passes, without its second
+                # population buffer
+                least = _separate_footprint(params)
+                if least == self.nbytes:
+                    raise
+                self.nbytes = least
+                self.workspace = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
             self.stream = torch.cuda.current_stream(self.device)
             self._h = lbm_create(params, self.workspace.data_ptr(), self.nbytes,
                                  self.stream.cuda_stream)
