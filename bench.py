@@ -60,10 +60,11 @@ def method_bytes_per_cell(Q, D, sp, s, lagged=False, m=0):
 
 
 def source_hash():
+    """Of every source of the library, so that a profile counts for one state of the kernels."""
     h = hashlib.sha256()
-    for rel in ("paper_2606_29619_amd/csrc/lbm_device.hpp", "paper_2606_29619_amd/csrc/lbm_host.hpp",
-                "paper_2606_29619_amd/csrc/lbm_launch.hpp", "paper_2606_29619_amd/csrc/lbm.hip"):
-        with open(os.path.join(ROOT, rel), "rb") as fh:
+    csrc = os.path.join(ROOT, "paper_2606_29619_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        with open(os.path.join(csrc, name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 

@@ -259,10 +259,12 @@ typedef struct lbm_solver lbm_solver;
 
 /*
  * Bytes of device workspace lbm_create uses for these parameters (pure host computation, no
- * device work).  Only lattice, storage, scheme, shift, nx, ny, nz, passes, whether mask is non-NULL
- * and the number of boundary nodes in bc_type are read.  D2Q9 two-pass runs that step in one launch
- * (see lbm_params.passes) count a second population buffer here; lbm_create also takes a workspace
- * without it (the footprint under LBM_PASSES_SEPARATE) and then steps in separate passes.
+ * device work).  Read are the lattice, storage, scheme, shift, dimensions, tiles, passes and
+ * picard_iters (all checked), whether mask and grad_eps are non-NULL, and, with bc_type, the
+ * boundary nodes and the mask around them (checked and counted).  D2Q9 two-pass runs that step
+ * in one launch (see lbm_params.passes) count a second population buffer here; lbm_create also
+ * takes a workspace without it (the footprint under LBM_PASSES_SEPARATE) and then steps in
+ * separate passes.
  * Errors: LBM_ERR_INVALID_ARG for NULL pointers or bad lattice, storage or dimensions.
  */
 LBM_API int lbm_footprint(const lbm_params *p, size_t *workspace_bytes);
@@ -365,8 +367,9 @@ LBM_API int lbm_lattice_info(int lattice, int *c_out, int *opp_out);
  *
  * Requests (each an lbm_params run with a steady-state tolerance) queue on submission and are
  * admitted in arrival order as memory of the caller's device pool frees up: a request whose
- * workspace (lbm_footprint) does not fit lets later, smaller ones pass (backfill) until it has
- * waited 64 rounds, after which admission waits for it.  Admitted requests keep their
+ * workspace (lbm_footprint under LBM_PASSES_SEPARATE: the batched passes step in place) does not
+ * fit lets later, smaller ones pass (backfill) until it has waited 64 rounds, after which
+ * admission waits for it.  Admitted requests keep their
  * populations resident and advance together in rounds of check_every steps: every pass of a
  * round is one kernel launch over the tiles of all active runs that share a lattice, storage,
  * solids flag, scheme and AA phase (kernel boundaries are the per-request step barriers), so
@@ -396,7 +399,7 @@ typedef struct lbm_request_info {
     double t_admit;          /* -1 until admitted */
     double t_done;           /* -1 until converged, censored or failed */
     int64_t cells;           /* nx * ny * nz */
-    size_t workspace_bytes;  /* lbm_footprint of the run */
+    size_t workspace_bytes;  /* lbm_footprint of the run under LBM_PASSES_SEPARATE */
 } lbm_request_info;
 
 typedef struct lbm_server_stats {

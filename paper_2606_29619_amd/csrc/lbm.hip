@@ -148,9 +148,10 @@ int check_handle(const lbm_solver *h) {
 // Tiles of a run.  FP32 and FP64 storage: packed rows for x extents that are not a multiple of 64,
 // in every pass, unless the caller asks for rectangular tiles.
 // 16-bit storage: the collision, which stages nothing, takes packed rows like FP32's on D3Q27 (FP16
-// 150^3 145 us packed, 180 rectangular; 200^3 306 and 469) and rectangular tiles on D2Q9; the moment and lagged passes choose for themselves (moment_tiles).  With solids the passes share one
-// set of tile flags and so one kind of tile: packed where a D3Q27 run's rectangular tiles would leave
-// at least 30 % of the lanes idle.
+// 150^3 145 us packed, 180 rectangular; 200^3 306 and 469) and rectangular tiles on D2Q9; the
+// moment and lagged passes choose for themselves (moment_tiles).  With solids the passes share one
+// set of tile flags and so one kind of tile: packed where a D3Q27 run's rectangular tiles would
+// leave at least 30 % of the lanes idle.
 RunTiles run_tiles(const lbm_params *p) {
     const int nx = p->nx, ny = p->ny, nz = p->nz, tx = rect_tile_x(nx, ny);
     const bool ragged = nx % 64 != 0 && p->tiles != LBM_TILES_RECTANGULAR;
@@ -173,13 +174,13 @@ RunTiles run_tiles(const lbm_params *p) {
 // 32 x 8 tiles.  One launch is possible for two-pass runs of 256 cells and more without wet nodes,
 // Picard iterations or analytic derivatives (a smaller grid has fewer cells than one workgroup has
 // threads) and taken where it is expected to be faster.  Each form's step is estimated from its
-// lanes, idle ones of tiles past the grid's edges included: least-squares fits to 71 shapes from
-// 1 x 1024 to 2000 x 2000 cells in each storage, periodic boxes and channels with walls.  The three
+// lanes, idle ones of tiles past the grid's edges included: least-squares fits to 71 shapes from 1
+// x 1024 to 2000 x 2000 cells in each storage, periodic boxes and channels with walls.  The three
 // dependent launches of the separate passes cost some 10 us however small the run; the tiles of one
-// launch form the records of their rings too, which a plane much thinner than a tile does not repay.
-// us per step, separate and one launch: FP64 channel with walls 128 x 64 13.6 and 7.3, 8 x 65,536
-// 50 and 160; FP32 box 1019 x 977 44.5 and 26.5, 1 x 262,140 17 and 237; FP16 8 x 65,536 100 and 55
-// (its separate passes take rectangular tiles), 65,536 x 1 10.9 and 15.1.
+// launch form the records of their rings too, which a plane much thinner than a tile does not
+// repay.  us per step, separate and one launch: FP64 channel with walls 128 x 64 13.6 and 7.3, 8 x
+// 65,536 50 and 160; FP32 box 1019 x 977 44.5 and 26.5, 1 x 262,140 17 and 237; FP16 8 x 65,536 100
+// and 55 (its separate passes take rectangular tiles), 65,536 x 1 10.9 and 15.1.
 PlaneShape plane_shape(const lbm_params *p, uint32_t nb) {
     if (p->lattice != LBM_D2Q9 || p->scheme != LBM_SCHEME_TWO_PASS || nb != 0 ||
         (int64_t)p->nx * p->ny < 256 || p->picard_iters != 0 || p->grad_eps ||

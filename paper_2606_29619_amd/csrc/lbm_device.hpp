@@ -9,7 +9,8 @@
 // porosity_correction_expanded).
 //
 // Storage: structure-of-arrays populations f[i][n], n = x + nx*(y + ny*z), one in-place buffer
-// streamed with the AA pattern:
+// streamed with the AA pattern (the one-launch D2Q9 step of lbm_plane.hpp writes the slots of the
+// same pattern in a second buffer):
 //   phase 0 (natural layout): cell n reads f_i from slot (i, n) and writes its post-collision
 //            value to slot (opp(i), n);
 //   phase 1 (swapped layout): cell n reads f_i from slot (opp(i), n - c_i) and writes to slot
@@ -20,8 +21,9 @@
 // the update is race-free in place.  Every axis wraps periodically.
 //
 // Addressing: every array plane (one population, one scalar field, or the packed four-value
-// moment records) holds fewer than 2^32 bytes, so a thread addresses it with a 32-bit byte offset added to a uniform 64-bit base (the scalar-base + vector-offset form of
-// the global memory instructions).  The periodic neighbours of a cell are precomputed once
+// moment records) holds fewer than 2^32 bytes, so a thread addresses it with a 32-bit byte offset
+// added to a uniform 64-bit base (the scalar-base + vector-offset form of the global memory
+// instructions).  The periodic neighbours of a cell are precomputed once
 // per thread (three x positions, nine y/z row bases).
 //
 // Floating point: built with -ffp-contract=off.  In FP64 every expression is evaluated exactly
@@ -132,22 +134,23 @@ __device__ __forceinline__ T ld(const T *base, uint32_t idx) {
     return *at(base, idx);
 }
 
-// Populations stream through once per kernel.  In the natural-layout phase each thread touches
-// only its own cell, and the accesses are non-temporal (the caches are left to the reused
-// moment and porosity fields).  In the swapped phase the x-shifted accesses (c_x != 0) of
-// neighbouring lanes and waves share cache lines, so they go through the caches normally, while
-// those with c_x = 0 cover whole lines of one wave and stay non-temporal (256^3 box: FP32 step
-// 1.236 -> 1.218 ms, FP32 lagged pass 1.050 -> 1.026 ms; the moment pass with every load of the
-// swapped phase non-temporal was 0.6 % slower than with this rule).
+// Populations stream through once per kernel.  In the natural-layout phase each thread touches only
+// its own cell, and the accesses are non-temporal (the caches are left to the reused moment and
+// porosity fields).  In the swapped phase the x-shifted accesses (c_x != 0) of neighbouring lanes
+// and waves share cache lines, so they go through the caches normally, while those with c_x = 0
+// cover whole lines of one wave and stay non-temporal (256^3 box: FP32 step 1.236 -> 1.218 ms, FP32
+// lagged pass 1.050 -> 1.026 ms; the moment pass with every load of the swapped phase non-temporal
+// was 0.6 % slower than with this rule).
 //
-// Template parameter PH of the passes: bit 0 the AA phase (0 natural, 1 swapped), bit 1 set where all
-// accesses go through the caches, which pays in two cases (cached_passes chooses):
-// a run whose populations, records and static fields stay in the 256 MB Infinity Cache from one pass
-// to the next (us per step, non-temporal and cached: FP32 box 70^3 46 -> 40, 100^3 97 -> 84, 115^3 153
-// -> 122, FP64 90^3 150 -> 124, FP32 lagged 100^3 77 -> 61; beyond, it costs: FP32 160^3 350 -> 380,
-// FP64 120^3 303 -> 335); and rows that are no whole 128-byte lines, whose ends waves share (FP16 220^3
-// collision 456 -> 387, lagged pass 671 -> 609, FP32 220^3 collision 609 -> 564, 150^3 208 -> 181; but
-// FP32 moment pass 271 -> 299, FP64 collision 145 -> 142 at 110^3 and 281 -> 286 at 140^3).
+// Template parameter PH of the passes: bit 0 the AA phase (0 natural, 1 swapped), bit 1 set where
+// all accesses go through the caches, which pays in two cases (cached_passes chooses): a run whose
+// populations, records and static fields stay in the 256 MB Infinity Cache from one pass to the
+// next (us per step, non-temporal and cached: FP32 box 70^3 46 -> 40, 100^3 97 -> 84, 115^3 153 ->
+// 122, FP64 90^3 150 -> 124, FP32 lagged 100^3 77 -> 61, with analytic derivatives and walls FP32
+// 64^3 35 -> 30; beyond, it costs: FP32 160^3 350 -> 380, FP64 120^3 303 -> 335); and rows that are
+// no whole 128-byte lines, whose ends waves share (FP16 220^3 collision 456 -> 387, lagged pass 671
+// -> 609, FP32 220^3 collision 609 -> 564, 150^3 208 -> 181; but FP32 moment pass 271 -> 299, FP64
+// collision 145 -> 142 at 110^3 and 281 -> 286 at 140^3).
 constexpr bool swapped(int ph) { return (ph & 1) != 0; }
 constexpr bool cached(int ph) { return (ph & 2) != 0; }
 template <bool NT, typename T>
@@ -392,12 +395,13 @@ __device__ __forceinline__ float shift_sigma(T e_src, const Phys<T> &ph) {
     }
 }
 
-// Value of a slot in arithmetic type A (FP32 in the kernels; FP64 for exact checkpoints).  Decode
-// and encode take 4 and 3 instructions per population (base, sigma, conversion, scaled sum) where
-// the unfused forms with a select of the shift rule took 6 and 4, of about 950 in the collision, 420
-// in the moment pass: the 16-bit passes are bound by vector issue as much as by memory.  256^3 FP16
-// fused collision 706 -> 678 us, 224^3 BF16 lagged pass 673 -> 618 us, FP16 200 x 100 x 100 duct step
-// 399 -> 294 us.
+// Value of a slot in arithmetic type A (FP32 in the kernels; FP64 for exact checkpoints).  The
+// scaled sums of decode and encode are one fused operation each and the shift base one multiply-add
+// (the conversion of an FP16 value is part of the decode's): the unfused forms with a select of the
+// shift rule were a quarter of the collision's vector instructions and half of the moment pass's,
+// and the 16-bit passes are bound by vector issue as much as by memory.  256^3 FP16 fused collision
+// 706 -> 678 us, 224^3 BF16 lagged pass 673 -> 618 us, FP16 200 x 100 x 100 duct step 399 -> 294
+// us.
 template <int D, int I, typename A, typename P>
 __device__ __forceinline__ A decode(P raw, float sigma) {
     if constexpr (!PopFmt<P>::shifted) {
@@ -457,11 +461,11 @@ __device__ __forceinline__ P load_raw(const P *__restrict__ f, const uint8_t *__
     }
 }
 
-// Shift of the f_I found at cell n (0 for FP64/FP32 storage): the porosity of its source cell,
-// the upstream neighbour n - c_I or n itself after a bounce-back.  Both shift rules
-// take one form (shift_base): a branch around the porosity read, which the lattice-weight shift does not
-// need, costs more than it spares in the collision (FP16 duct 384 x 192 x 192 without and with it:
-// porous shift 762 and 1,087 us, weights 762 and 837; 200^3 274 and 300, 274 and 265) and where the
+// Shift of the f_I found at cell n (0 for FP64/FP32 storage): the porosity of its source cell, the
+// upstream neighbour n - c_I or n itself after a bounce-back.  Both shift rules take one form
+// (shift_base): a branch around the porosity read, which the lattice-weight shift does not need,
+// costs more than it spares in the collision (FP16 duct 384 x 192 x 192 without and with it: porous
+// shift 762 and 1,087 us, weights 762 and 837; 200^3 274 and 300, 274 and 265) and where the
 // porosity lies in LDS (256^3 moment pass 275 and 293).  load_pop's EARLY is for the rest.
 template <int D, bool SOLIDS, int I, typename P, typename T, typename E>
 __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, const E &ev,
@@ -995,8 +999,8 @@ __device__ __forceinline__ void cell_equilibria(const P4<T> *__restrict__ m2, co
 
 // ------------------------------------------------------------------------------------------
 // Kernels, one thread per cell.  A workgroup of 256 threads owns a tx x ty x 1 tile
-// (tx * ty = 256, tx = 256 for rows of 192 cells or more, so that the x-shifted accesses of the
-// swapped AA phase stay inside one workgroup), or, with packed rows, 256 consecutive cells of a
+// (tx * ty = 256, the width chosen by tile_x: the wider, the fewer x-shifted accesses of the
+// swapped AA phase leave the workgroup), or, with packed rows, 256 consecutive cells of a
 // plane (see Tiling::packed).  Tiles are ordered so that stencil neighbours
 // are processed close in time on the same XCD: the (tile-row, plane) grid is cut into blocks of
 // by x bz tile rows, each block is traversed x-fastest then y then z, the blocks y-fastest then
@@ -1303,18 +1307,17 @@ __device__ __forceinline__ void load_pair_group(const P *__restrict__ f,
     });
 }
 
-// Collision and streaming of the cell's populations with the equilibria peq, pst.  The
-// populations are loaded only after the forcing arguments (FP32 / FP64 storage: except pair
-// groups [0, FIRST), which the caller loaded into fa), in pair groups, so that fewer registers
-// are live and more waves share each SIMD (16-bit storage: 3 -> 4 waves, 22 % faster).  With
-// FP32 / FP64 storage the loads of group k + 1 are issued before the stores of group k, which
-// can only reach slots that group k's own loads read (the AA pattern's slot of a population is
-// read and written by the same cell, and a group holds whole opposite pairs): 256^3 box, FP32
-// fused correction-collision kernel 0.885 -> 0.846 ms, FP64 2.05 -> 1.96 ms; the 16-bit forms
-// load, decode, collide and store one group after the other (pipelined, their fused kernel
-// spills: 0.75 -> 0.83 ms).
-// WEIGHTS: 16-bit storage under the lattice-weight shift, known at compile time, reads no porosity to
-// decode (every sigma is a constant); false serves both shift rules.
+// Collision and streaming of the cell's populations with the equilibria peq, pst.  The populations
+// are loaded only after the forcing arguments (FP32 / FP64 storage: except pair groups [0, FIRST),
+// which the caller loaded into fa), in pair groups, so that fewer registers are live and more waves
+// share each SIMD (16-bit storage: 3 -> 4 waves, 22 % faster).  With FP32 / FP64 storage the loads
+// of group k + 1 are issued before the stores of group k, which can only reach slots that group k's
+// own loads read (the AA pattern's slot of a population is read and written by the same cell, and a
+// group holds whole opposite pairs): 256^3 box, FP32 fused correction-collision kernel 0.885 ->
+// 0.846 ms, FP64 2.05 -> 1.96 ms; the 16-bit forms load, decode, collide and store one group after
+// the other (pipelined, their fused kernel spills: 0.75 -> 0.83 ms).
+// WEIGHTS: 16-bit storage under the lattice-weight shift, known at compile time, reads no porosity
+// to decode (every sigma is a constant); false serves both shift rules.
 template <int D, typename T, typename P, bool SOLIDS, int PH, int FIRST = 0, bool WEIGHTS = false,
           typename E>
 __device__ __forceinline__ void collide_populations(P *__restrict__ f,
@@ -1523,11 +1526,11 @@ __global__ __launch_bounds__(256) void k_picard(const P4<T> *__restrict__ vin,
     picard_body<D, T, SOLIDS, AD>(vin, m0, eps, muD, muF, mask, vout, g, tl, ph, omega, blockIdx.x);
 }
 
-// The moment and lagged passes of a tile: 16-bit storage stages the porosity its decode reads
-// in LDS on rectangular tiles and reads it through the caches on packed rows (ragged x extents of
+// The moment and lagged passes of a tile: 16-bit storage stages the porosity its decode reads in
+// LDS on rectangular tiles and reads it through the caches on packed rows (ragged x extents of
 // D3Q27 runs), whose tiles have no rectangular halo; there the lattice-weight shift, which needs no
-// porosity to decode, leaves early (FP16 66 x 192 x 160 without and with it: moment pass 52 and 28 us,
-// lagged pass 140 and 77).  Same values either way.
+// porosity to decode, leaves early (FP16 66 x 192 x 160 without and with it: moment pass 52 and 28
+// us, lagged pass 140 and 77).  Same values either way.
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
 __device__ __forceinline__ void moments_body(const P *__restrict__ f, const T *__restrict__ eps,
                                              const T *__restrict__ muD, const T *__restrict__ muF,
@@ -1570,9 +1573,10 @@ __device__ __forceinline__ void fused_body(P *__restrict__ f, const P4<T> *__res
 // the same expressions.  Bit k of tsolid[w] (k_tile_solid) tells whether a solid cell lies within
 // one cell (in any direction) of a cell of wave k of tile w; null means everywhere.  The passes
 // choose per wave; those that stage porosity in LDS (STAGED, 16-bit storage) choose per tile, as
-// all waves of a tile then meet at a barrier.  In a duct with solid x faces every tile of a row of
-// 384 cells touches a solid, but only two of its six waves (384 x 192 x 192, FP32: swapped-phase
-// collision 1,044 -> 890 us with the address selects of load_raw and store_pop, natural 886 -> 880).
+// all waves of a tile then meet at a barrier.  In a duct with solid x faces the tiles at both ends
+// of a row touch a solid, but only one of their two waves of the row does (384 x 192 x 192 FP32,
+// measured with tiles of 256 cells, both of which touch one: swapped-phase collision 1,044 -> 890
+// us with the address selects of load_raw and store_pop, natural 886 -> 880).
 template <bool STAGED>
 __device__ __forceinline__ bool solid_free(const uint8_t *__restrict__ tsolid) {
     if (!tsolid) return false;
@@ -1624,8 +1628,8 @@ __device__ __forceinline__ void vcorrect_flat_body(const P4<T> *__restrict__ own
 }
 
 // ST: StoreRec in a step; StoreMoments where the caller asks for the moments, whose records would
-// otherwise be written and read again by a pass of their own (FP32 128^3: 24 + 12.5 -> 26 us; a run of
-// ten 256^3 FP32 lagged steps and one read 11.02 -> 10.91 ms).
+// otherwise be written and read again by a pass of their own (FP32 128^3: 24 + 12.5 -> 26 us; a run
+// of ten 256^3 FP32 lagged steps and one read 11.02 -> 10.91 ms).
 template <int D, typename T, bool SOLIDS, bool AD, typename ST>
 __global__ __launch_bounds__(256) void k_vcorrect(const P4<T> *__restrict__ own_src,
                                                   const P4<T> *__restrict__ m1,
@@ -1744,9 +1748,9 @@ struct EpsRing {
     }
 };
 
-// WEIGHTS: see collide_populations; an instantiation of its own for that rule (256^3 FP16 box, fused
-// kernel: porous shift 678 us; lattice-weight shift 640 us, 679 us through the common form; both
-// rules in one kernel, chosen at run time, 728 and 707 us).
+// WEIGHTS: see collide_populations; an instantiation of its own for that rule (256^3 FP16 box,
+// fused kernel: porous shift 678 us; lattice-weight shift 640 us, 679 us through the common form;
+// both rules in one kernel, chosen at run time, 728 and 707 us).
 template <typename T, typename PS, int PH, bool WEIGHTS>
 __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__restrict__ f,
                                                           const P4<T> *__restrict__ m1,
@@ -1758,7 +1762,8 @@ __global__ __launch_bounds__((ZCfg<T, PS>::kThreads)) void k_collide_vc(PS *__re
     using C = ZCfg<T, PS>;
     constexpr int kZX = C::kX, kZY = C::kY, kZRX = C::kRX, kZRY = C::kRY, kZR = C::kR;
     constexpr int kZSX = C::kSX, kZS = C::kS, kZProd = C::kProd;
-    // (rho, v) of four consecutive planes on the tile and its ring: slot of plane z (z - z0 + 4) & 3
+    // (rho, v) of four consecutive planes on the tile and its ring: plane z in slot
+    // (z - z0 + 4) & 3
     __shared__ P4<T> vr[4][kZR];
     // (rho, v^(1)) records of four consecutive planes on the tile and two rings (kZSX x kZSY
     // cells), the correcting waves' inputs: slot of plane z (z - z0 + 8) & 3; porosity of six
@@ -1945,9 +1950,10 @@ void k_fused(P *__restrict__ f, const P4<T> *__restrict__ m1p, const P4<T> *__re
                                         blockIdx.x);
 }
 
-// Bit k of tsolid[w] = 1 when a cell of wave k (cells 64 k .. 64 k + 63) of tile w, or a cell within
-// one cell of one of them (faces, edges and corners, through the periodic wrap), is solid.  Same grid and tile order as the passes;
-// workgroups past the last tile write nothing (the passes return before reading theirs).
+// Bit k of tsolid[w] = 1 when a cell of wave k (cells 64 k .. 64 k + 63) of tile w, or a cell
+// within one cell of one of them (faces, edges and corners, through the periodic wrap), is solid.
+// Same grid and tile order as the passes; workgroups past the last tile write nothing (the passes
+// return before reading theirs).
 template <int D>
 __global__ __launch_bounds__(256) void k_tile_solid(const uint8_t *__restrict__ mask, Grid g,
                                                     Tiling tl, uint8_t *__restrict__ tsolid) {

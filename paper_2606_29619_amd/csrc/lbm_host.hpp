@@ -133,7 +133,8 @@ struct lbm_solver {
     lbm::Tiling tiles;  // 256-cell tiles, blocked, in XCD-contiguous ranges: collision and others
     lbm::Tiling mtiles; // the same of the moment and lagged passes (see run_tiles)
     bool fused_vc;      // velocity correction inside the collision pass (k_collide_vc)
-    lbmh::PlaneShape plane;  // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
+    // whole step in one launch (k_plane_step): phase 0 in L.f, phase 1 in L.f2
+    lbmh::PlaneShape plane;
     bool solid_occ;     // runs with solids: under a quarter of the tiles solid-aware
     bool cached_mom, cached_col, cached_lag;  // cached population accesses (see lbm::cached)
     lbm::ZTiling ztiles;
@@ -212,10 +213,10 @@ inline lbm::ZTiling make_ztiling(int nx, int ny, int nz, int tx, int ty) {
     return z;
 }
 
-// Width of the rectangular row tiles (256 x 1, 128 x 2 or 64 x 4 cells) of an nx x ny plane: the one
-// with the fewest lanes past the grid's edges, times `factor` for each doubling of the width.  Lanes
-// past a row's end idle in a working wave; a row past the plane's edge is a wave that ends early and
-// counts `edge` of one.
+// Width of the rectangular row tiles (256 x 1, 128 x 2 or 64 x 4 cells) of an nx x ny plane: the
+// one with the fewest lanes past the grid's edges, times `factor` for each doubling of the width.
+// Lanes past a row's end idle in a working wave; a row past the plane's edge is a wave that ends
+// early and counts `edge` of one.
 inline int tile_x(int nx, int ny, double factor, double edge, double *lanes = nullptr) {
     int best = 0;
     double cost = 0.0, f = 1.0;
@@ -232,11 +233,11 @@ inline int tile_x(int nx, int ny, double factor, double edge, double *lanes = nu
     return best;
 }
 
-// Width for the passes that stage nothing: a wider tile is worth 3 % of idle lanes per doubling (fewer
-// tile edges in x).  us per step of the separate FP32 passes at widths 64 / 128 / 256: 320 x 192 x 150
-// 823 / 828 / 1,023; 384 x 192 x 192 1,280 / 1,251 / 1,443; 448 x 160 x 100 617 / 659 / 650;
-// 256 x 192 x 192 869 / 857 / 827; FP64 192^3 1,319 / 1,507 / 1,340.  Few rows, 64 and 256 wide: FP32
-// 192 x 1 x 4096 66 / 58, 448 x 3 x 2048 215 / 224, FP64 473 / 495.
+// Width for the passes that stage nothing: a wider tile is worth 3 % of idle lanes per doubling
+// (fewer tile edges in x).  us per step of the separate FP32 passes at widths 64 / 128 / 256: 320 x
+// 192 x 150 823 / 828 / 1,023; 384 x 192 x 192 1,280 / 1,251 / 1,443; 448 x 160 x 100 617 / 659 /
+// 650; 256 x 192 x 192 869 / 857 / 827; FP64 192^3 1,319 / 1,507 / 1,340.  Few rows, 64 and 256
+// wide: FP32 192 x 1 x 4096 66 / 58, 448 x 3 x 2048 215 / 224, FP64 473 / 495.
 inline int rect_tile_x(int nx, int ny) { return tile_x(nx, ny, 0.97, 0.12); }
 
 // Tiles of the cell passes: rectangular tiles of tx cells along x, or packed rows, so that rows of,
@@ -254,19 +255,19 @@ inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
 }
 
 // Tiles of the 16-bit moment and lagged passes without solids.
-// Rectangular tiles stage the porosity of the decode (the 26 neighbours of a D3Q27 cell) in LDS.  The
-// narrowest has the smallest halo (64 x 4: 1,188 values, 256 x 1: 2,322), which the moment pass feels
-// (256 x 192 x 192 FP16, widths 64 / 128 / 256: 161 / 173 / 184 us) and the lagged pass hardly (224^3
-// BF16 675 / 672 / 687 us) except on D2Q9, where it has less else to do (65,536 x 3: 7.4 and 9.4 us);
-// but three of its four rows lie past the edge of a plane of one row, and each stages all the same
-// (256 x 1 x 4096 FP16, 64 and 256 wide: moments 44 and 26 us, lagged 86 and 52; 512 x 3 x 2048 lagged
-// 171 and 160).
+// Rectangular tiles stage the porosity of the decode (the 26 neighbours of a D3Q27 cell) in LDS.
+// The narrowest has the smallest halo (64 x 4: 1,188 values, 256 x 1: 2,322), which the moment pass
+// feels (256 x 192 x 192 FP16, widths 64 / 128 / 256: 161 / 173 / 184 us) and the lagged pass
+// hardly (224^3 BF16 675 / 672 / 687 us) except on D2Q9, where it has less else to do (65,536 x 3:
+// 7.4 and 9.4 us); but three of its four rows lie past the edge of a plane of one row, and each
+// stages all the same (256 x 1 x 4096 FP16, 64 and 256 wide: moments 44 and 26 us, lagged 86 and
+// 52; 512 x 3 x 2048 lagged 171 and 160).
 // Packed rows (can_pack: a ragged D3Q27 run) read that porosity through the caches, at some three
 // times the moment pass's time per lane under the porous shift and over twice the lagged pass's
-// (packed and rectangular, 192 x 160 rows of 9 cells: moments 13 and 31 us, lagged 25 and 77; of 25:
-// 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).  The
-// lattice-weight shift needs none of it, and packing pays from a fifth of idle lanes (192 x 160 rows
-// of 66: moments 28 and 52 us, of 17: 11 and 30; 150^3 lagged 173 and 206).
+// (packed and rectangular, 192 x 160 rows of 9 cells: moments 13 and 31 us, lagged 25 and 77; of
+// 25: 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).
+// The lattice-weight shift needs none of it, and packing pays from a fifth of idle lanes (192 x 160
+// rows of 66: moments 28 and 52 us, of 17: 11 and 30; 150^3 lagged 173 and 206).
 inline lbm::Tiling moment_tiles(int nx, int ny, int nz, bool d3, bool can_pack, bool lagged,
                                 bool weights) {
     double lanes;
@@ -313,10 +314,10 @@ RunTiles run_tiles(const lbm_params *p);
 
 // Which passes access the populations through the caches: all when the step's working set (bytes)
 // stays in the Infinity Cache, and on rows that are no whole cache lines the collision of FP32 and
-// 16-bit storage and the 16-bit moment and lagged passes on staged tiles (measured at lbm::cached; the
-// largest sets that gained held 231 MB, the smallest that lost 280 MB).  On packed rows those two lose
-// like FP32's moment pass (FP16, lattice-weight shift, non-temporal and cached: 200^3 moments 120 and
-// 135 us, 81 x 256 x 256 74 and 91; 81 x 192 x 160 lagged pass 111 and 121).
+// 16-bit storage and the 16-bit moment and lagged passes on staged tiles (measured at lbm::cached;
+// the largest sets that gained held 231 MB, the smallest that lost 280 MB).  On packed rows those
+// two lose like FP32's moment pass (FP16, lattice-weight shift, non-temporal and cached: 200^3
+// moments 120 and 135 us, 81 x 256 x 256 74 and 91; 81 x 192 x 160 lagged pass 111 and 121).
 constexpr int64_t kCachedSet = 240 << 20;
 struct CachedPasses {
     bool moments, collide, lagged;

@@ -169,9 +169,6 @@ void launch_stats(const lbm_solver *h, size_t m2, double *part) {
 }
 
 // ---- wet-node boundary kernels (one thread per boundary node; boundaries imply solids) -----
-// The rebuild writes populations through the caches, as the collision reads them next (384 x 192 x 192
-// FP32 duct, rebuild and collision 950 -> 923 us; 150 x 100 x 100, where every pass does so, 111 -> 94);
-// the records' reads gain nothing from it (56 -> 75 us in the larger duct) and keep the hints.
 template <typename T>
 lbm::BNodes<T> bnodes_of(const lbm_solver *h) {
     return lbm::BNodes<T>{ws_ptr<const uint32_t>(h, h->L.bcell), ws_ptr<const uint32_t>(h, h->L.bcode),
@@ -222,6 +219,10 @@ struct BcFixPass {
                                bnodes_of<T>(h));
     }
 };
+// The rebuild writes populations through the caches, as the collision reads them next (384 x 192 x
+// 192 FP32 duct, rebuild and collision 950 -> 923 us; 150 x 100 x 100, where every pass does so,
+// 111 -> 94); the records' reads gain nothing from it (56 -> 75 us in the larger duct) and keep the
+// hints.
 struct BcRebuildPass {  // own records m2, stencil neighbours' nbr
     static constexpr bool kDerivs = true;
     const lbm_solver *h;

@@ -19,14 +19,14 @@ void launch(const lbm_solver *h) {
                        grid_of(h), ntx, nt, per, phys_of<T>(h));
 }
 
-// Small tiles have the shortest chain of loads and barriers (with solids every thread forms one record,
-// without 144 of the 256 do), and the ring cells computed again cost nothing on an idle chip.  On
-// larger planes the ring cells' arithmetic counts and the tile is 32 x 8 (whole 128-byte lines in FP32,
-// 1.7 records per cell against 2.25); plane_shape chooses.  us per step, 8 x 8 against 32 x 8: FP64
-// channel with walls 128 x 64 7.3 / 11.3, 320 x 160 11.0 / 11.3; FP32 box 200 x 200 4.9 / 5.8,
-// 256 x 256 6.0 / 5.9, 512 x 512 13.2 / 10.0, 1024 x 1024 39.5 / 27.9; FP64 200 x 200 7.6 / 8.0,
-// 256 x 256 9.0 / 8.4 (16 x 16, 64 x 8 and 64 x 16 tiles within 4 % of 32 x 8 on large planes, slower
-// on small ones).
+// Small tiles have the shortest chain of loads and barriers (with solids every thread forms one
+// record, without 144 of the 256 do), and the ring cells computed again cost nothing on an idle
+// chip.  On larger planes the ring cells' arithmetic counts and the tile is 32 x 8 (whole 128-byte
+// lines in FP32, 1.7 records per cell against 2.25); plane_shape chooses.  us per step, 8 x 8
+// against 32 x 8: FP64 channel with walls 128 x 64 7.3 / 11.3, 320 x 160 11.0 / 11.3; FP32 box 200
+// x 200 4.9 / 5.8, 256 x 256 6.0 / 5.9, 512 x 512 13.2 / 10.0, 1024 x 1024 39.5 / 27.9; FP64 200 x
+// 200 7.6 / 8.0, 256 x 256 9.0 / 8.4 (16 x 16, 64 x 8 and 64 x 16 tiles within 4 % of 32 x 8 on
+// large planes, slower on small ones).
 template <typename T, typename P, bool S, int PH>
 void launch_shape(const lbm_solver *h) {
     if (h->plane == kPlaneSmall) launch<T, P, S, PH, 8, 8, 256>(h);

@@ -1,18 +1,18 @@
 // lbm_plane.hpp -- the two-pass D2Q9 step in one launch.
 //
-// The separate passes of a D2Q9 step each move little and mostly wait (memory latency and the
-// drain between dependent launches): a workgroup here takes the whole step of a tile of the
-// plane instead.  It forms the records (rho, v^(1)) of the tile and kRM rings around it from the
+// The separate passes of a D2Q9 step each move little and mostly wait (memory latency and the drain
+// between dependent launches): a workgroup here takes the whole step of a tile of the plane
+// instead.  It forms the records (rho, v^(1)) of the tile and kRM rings around it from the
 // populations, the corrected velocities of the tile and kRV rings from those, and collides the
-// tile, all through LDS; ring cells are computed again by the neighbouring tiles.  As a tile
-// reads its neighbours' populations, the step reads one population buffer and writes the other
-// (slot for slot what the in-place passes write).  Every expression is the separate passes' own,
-// so results are bitwise the same.
+// tile, all through LDS; ring cells are computed again by the neighbouring tiles.  As a tile reads
+// its neighbours' populations, the step reads one population buffer and writes the other (slot for
+// slot what the in-place passes write).  Every expression is the separate passes' own, so results
+// are bitwise the same.
 //
 // Bounded by vector arithmetic on large planes (FP32 1019 x 977: 84 B per cell and step, 14 us at
-// the copy rate, against 26 us) and by one tile's chain of load latencies and barriers on small ones.
-// us per step, separate passes and one launch: FP64 channel with walls 128 x 64 13.6 -> 7.3, FP32
-// box 1019 x 977 44.5 -> 26.5.
+// the copy rate, against 26 us) and by one tile's chain of load latencies and barriers on small
+// ones.  us per step, separate passes and one launch: FP64 channel with walls 128 x 64 13.6 -> 7.3,
+// FP32 box 1019 x 977 44.5 -> 26.5.
 #pragma once
 
 #include "lbm_device.hpp"
