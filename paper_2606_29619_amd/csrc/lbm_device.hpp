@@ -109,8 +109,8 @@ __device__ __forceinline__ float dv(float a, float b) { return a * __builtin_amd
 // mass steadily with it).
 __device__ __forceinline__ double div_rn(double a, double b) { return a / b; }
 __device__ __forceinline__ float div_rn(float a, float b) { return a / b; }
-// a b + c where the product is exact (a power of two, or a sum with an exact zero): the fused form
-// then rounds as the two operations do.
+// a b + c where the product is exact (by a power of two): the fused form then rounds as the two
+// operations do.
 __device__ __forceinline__ double mad_exact(double a, double b, double c) { return a * b + c; }
 __device__ __forceinline__ float mad_exact(float a, float b, float c) {
     return __builtin_fmaf(a, b, c);
@@ -347,13 +347,13 @@ struct PopFmt {
 };
 template <>
 struct PopFmt<_Float16> {
-    static constexpr bool shifted = true;
+    static constexpr bool shifted = true, mad_once = true;
     __device__ static __forceinline__ float dec(_Float16 h) { return (float)h; }
     __device__ static __forceinline__ _Float16 enc(float x) { return (_Float16)x; }
 };
 template <>
 struct PopFmt<__bf16> {
-    static constexpr bool shifted = true;
+    static constexpr bool shifted = true, mad_once = false;
     __device__ static __forceinline__ float dec(__bf16 h) { return (float)h; }
     __device__ static __forceinline__ __bf16 enc(float x) { return (__bf16)x; }
 };
@@ -411,13 +411,25 @@ __device__ __forceinline__ A decode(P raw, float sigma) {
         return mad_exact((A)PopFmt<P>::dec(raw), (A)dscale, (A)sigma);
     }
 }
+// a b + c rounded once to FP16, b uniform.  One instruction by name: whether the compiler selects it
+// for the conversion of an FP32 fused multiply-add, which rounds twice otherwise, varies from kernel
+// to kernel, and a run's result must not depend on the kernels (tiles, passes, server) it takes.
+__device__ __forceinline__ _Float16 mad_half(float a, float b, float c) {
+    _Float16 h;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(a), "s"(b), "v"(c));
+    return h;
+}
+// The value (v - sigma) escale, rounded once for FP16; for BF16 (no such instruction) and from FP64
+// (checkpoints) the FP32 value is rounded again.
 template <int D, int I, typename P, typename A>
 __device__ __forceinline__ P encode(A v, float sigma) {
     if constexpr (!PopFmt<P>::shifted) {
         return (P)v;
     } else {
         constexpr float escale = enc_scale<D, I>();
-        return PopFmt<P>::enc((float)mad_exact(v, (A)escale, -((A)sigma * (A)escale)));
+        const A offset = -((A)sigma * (A)escale);
+        if constexpr (sizeof(A) == 4 && PopFmt<P>::mad_once) return mad_half(v, escale, offset);
+        else return PopFmt<P>::enc((float)mad_exact(v, (A)escale, offset));
     }
 }
 
