@@ -478,7 +478,7 @@ __device__ __forceinline__ P load_raw(const P *__restrict__ f, const uint8_t *__
 // (shift_base): a branch around the porosity read, which the lattice-weight shift does not need,
 // costs more than it spares in the collision (FP16 duct 384 x 192 x 192 without and with it: porous
 // shift 762 and 1,087 us, weights 762 and 837; 200^3 274 and 300, 274 and 265) and where the
-// porosity lies in LDS (256^3 moment pass 275 and 293).  load_pop's EARLY is for the rest.
+// porosity lies in LDS (256^3 moment pass 275 and 293).  load_pop's SHIFT is for the rest.
 template <int D, bool SOLIDS, int I, typename P, typename T, typename E>
 __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, const E &ev,
                                             const Phys<T> &ph, const Nbr<D> &nb) {
@@ -496,14 +496,16 @@ __device__ __forceinline__ float load_sigma(const uint8_t *__restrict__ mask, co
     }
 }
 
-// EARLY: a uniform branch spares the lattice-weight shift the read of the source cell's porosity.
-template <int D, bool SOLIDS, int PH, int I, bool EARLY = false, typename T, typename P, typename E>
+// SHIFT: how the lattice-weight shift, which needs no porosity, is spared the read of the source
+// cell's: not (0), by a uniform branch (1), or at compile time, in code for that shift alone (2).
+template <int D, bool SOLIDS, int PH, int I, int SHIFT = 0, typename T, typename P, typename E>
 __device__ __forceinline__ T load_pop(const P *__restrict__ f, const uint8_t *__restrict__ mask,
                                       const E &ev, const Phys<T> &ph, const Grid &g,
                                       const Nbr<D> &nb) {
     const P raw = load_raw<D, SOLIDS, PH, I>(f, mask, g, nb);
-    if constexpr (EARLY && PopFmt<P>::shifted) {
-        if (ph.shift_a == 0.0f) return decode<D, I, T>(raw, ph.shift_b * weight<D, I>());
+    if constexpr (SHIFT != 0 && PopFmt<P>::shifted) {
+        if (SHIFT == 2 || ph.shift_a == 0.0f)
+            return decode<D, I, T>(raw, ph.shift_b * weight<D, I>());
     }
     return decode<D, I, T>(raw, load_sigma<D, SOLIDS, I, P>(mask, ev, ph, nb));
 }
@@ -1227,7 +1229,8 @@ __device__ __forceinline__ void collide_stream(P *__restrict__ f,
 
 // Pass one of the two-pass scheme: the record (rho, v^(1)) of every cell.  STAGE: the porosity
 // of the tile and its halo is staged in LDS (16-bit storage on rectangular tiles).
-template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD, bool STAGE>
+template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD, bool STAGE,
+          int SHIFT = 0>
 __device__ __forceinline__ void moments_body_s(const P *__restrict__ f,
                                                  const T *__restrict__ eps,
                                                  const T *__restrict__ muD,
@@ -1247,7 +1250,7 @@ __device__ __forceinline__ void moments_body_s(const P *__restrict__ f,
     T fi[L::Q];
     unroll<0, L::Q>([&](auto ii) {
         constexpr int i = decltype(ii)::value;
-        fi[i] = load_pop<D, SOLIDS, PH, i, !STAGE && !SOLIDS>(f, mask, ev, ph, g, nb);
+        fi[i] = load_pop<D, SOLIDS, PH, i, SHIFT>(f, mask, ev, ph, g, nb);
     });
     T v0[3];
     const Rec<T> q = cell_moments<D, AD>(fi, ev, muD, muF, nb, ph, m0_out ? v0 : nullptr);
@@ -1464,7 +1467,7 @@ __device__ __forceinline__ void fused_body_s(P *__restrict__ f, const P4<T> *__r
     T fi[L::Q];
     unroll<0, L::Q>([&](auto ii) {
         constexpr int i = decltype(ii)::value;
-        fi[i] = load_pop<D, SOLIDS, PH, i, !STAGE && !SOLIDS>(f, mask, ev, ph, g, nb);
+        fi[i] = load_pop<D, SOLIDS, PH, i, !STAGE && !SOLIDS ? 1 : 0>(f, mask, ev, ph, g, nb);
     });
     const Rec<T> own1 = cell_moments<D, AD>(fi, ev, muD, muF, nb, ph);
     const CellStatic<D, T> cs = cell_static<D, AD>(ev, ph, n, own1.e);
@@ -1540,9 +1543,12 @@ __global__ __launch_bounds__(256) void k_picard(const P4<T> *__restrict__ vin,
 
 // The moment and lagged passes of a tile: 16-bit storage stages the porosity its decode reads in
 // LDS on rectangular tiles and reads it through the caches on packed rows (ragged x extents of
-// D3Q27 runs), whose tiles have no rectangular halo; there the lattice-weight shift, which needs no
-// porosity to decode, leaves early (FP16 66 x 192 x 160 without and with it: moment pass 52 and 28
-// us, lagged pass 140 and 77).  Same values either way.
+// D3Q27 runs), whose tiles have no rectangular halo; there the lattice-weight shift reads none (FP16
+// 66 x 192 x 160, porosity staged and not read: moment pass 52 and 28 us, lagged pass 140 and 90),
+// in a body of its own in the moment pass and behind a branch per population in the lagged one: the
+// branch takes the batched moment pass from 62 to 68 registers and its other runs from 65 to 69 us
+// (swapped phase), the body slows the lagged pass's others by 5 % (256^3 828 -> 865 us).  Same
+// values either way.
 template <int D, typename T, typename P, bool SOLIDS, int PH, bool AD>
 __device__ __forceinline__ void moments_body(const P *__restrict__ f, const T *__restrict__ eps,
                                              const T *__restrict__ muD, const T *__restrict__ muF,
@@ -1551,8 +1557,12 @@ __device__ __forceinline__ void moments_body(const P *__restrict__ f, const T *_
                                              Grid g, Tiling tl, Phys<T> ph, uint32_t wg) {
     if constexpr (PopFmt<P>::shifted && D == 3) {
         if (tl.packed) {
-            moments_body_s<D, T, P, SOLIDS, PH, AD, false>(f, eps, muD, muF, mask, m1_out, m0_out,
-                                                           g, tl, ph, wg);
+            if (!SOLIDS && ph.shift_a == 0.0f)
+                moments_body_s<D, T, P, SOLIDS, PH, AD, false, SOLIDS ? 0 : 2>(
+                    f, eps, muD, muF, mask, m1_out, m0_out, g, tl, ph, wg);
+            else
+                moments_body_s<D, T, P, SOLIDS, PH, AD, false>(f, eps, muD, muF, mask, m1_out,
+                                                               m0_out, g, tl, ph, wg);
             return;
         }
     }

@@ -267,7 +267,7 @@ inline lbm::Tiling make_tiling(int nx, int ny, int nz, bool packed, int tx) {
 // (packed and rectangular, 192 x 160 rows of 9 cells: moments 13 and 31 us, lagged 25 and 77; of
 // 25: 33 and 30, 51 and 72; of 37: 46 and 30, 96 and 72; 256 x 256 rows of 30: lagged 159 and 146).
 // The lattice-weight shift needs none of it, and packing pays from a fifth of idle lanes (192 x 160
-// rows of 66: moments 28 and 52 us, of 17: 11 and 30; 150^3 lagged 173 and 206).
+// rows of 66: moments 28 and 52 us, of 17: 11 and 30; 150^3 lagged 184 and 206).
 inline lbm::Tiling moment_tiles(int nx, int ny, int nz, bool d3, bool can_pack, bool lagged,
                                 bool weights) {
     double lanes;
@@ -314,10 +314,11 @@ RunTiles run_tiles(const lbm_params *p);
 
 // Which passes access the populations through the caches: all when the step's working set (bytes)
 // stays in the Infinity Cache, and on rows that are no whole cache lines the collision of FP32 and
-// 16-bit storage and the 16-bit moment and lagged passes on staged tiles (measured at lbm::cached;
-// the largest sets that gained held 231 MB, the smallest that lost 280 MB).  On packed rows those
-// two lose like FP32's moment pass (FP16, lattice-weight shift, non-temporal and cached: 200^3
-// moments 120 and 135 us, 81 x 256 x 256 74 and 91; 81 x 192 x 160 lagged pass 111 and 121).
+// 16-bit storage and the 16-bit moment and lagged passes, these two not on packed rows without
+// solids (measured at lbm::cached; the largest sets that gained held 231 MB, the smallest that lost
+// 280 MB).  There they lose like FP32's moment pass (FP16, lattice-weight shift, non-temporal and
+// cached: 200^3 moments 120 and 135 us, 81 x 256 x 256 74 and 91; 81 x 192 x 160 lagged pass 111 and
+// 121; with solids, 70 x 192 x 192 moments 101 and 92).
 constexpr int64_t kCachedSet = 240 << 20;
 struct CachedPasses {
     bool moments, collide, lagged;
@@ -338,12 +339,15 @@ inline int64_t step_bytes(const lbm_solver *h) {
     const int sp = h->storage == LBM_F64 ? 8 : (h->storage == LBM_F32 ? 4 : 2);
     return h->N * (h->Q * sp + (3 + (h->scheme == LBM_SCHEME_LAGGED ? 16 : 8)) * s);
 }
-// Rows of populations that are no whole cache lines, and such rows under rectangular moment tiles.
+// Rows of populations that are no whole cache lines, and such rows in runs that have solids or whose
+// moment tiles are not packed.
 inline bool ragged_lines(const lbm_solver *h) {
     const int sp = h->storage == LBM_F64 ? 8 : (h->storage == LBM_F32 ? 4 : 2);
     return (int64_t)h->nx * sp % 128 != 0;
 }
-inline bool staged_ragged(const lbm_solver *h) { return ragged_lines(h) && !h->mtiles.packed; }
+inline bool staged_ragged(const lbm_solver *h) {
+    return ragged_lines(h) && (h->solids || !h->mtiles.packed);
+}
 
 // Workspace layout of a run with the shape and options of p (validates them; host only).
 int run_layout(const lbm_params *p, Layout *L);
